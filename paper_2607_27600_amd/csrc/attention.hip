@@ -15,7 +15,7 @@
 //   K and V tiles go from global memory straight into LDS (no register staging), both
 //   row-major with XOR-swizzled 16-byte chunks; the V^T operand of the second product is
 //   read with LDS transpose reads.  Both are double buffered with one barrier per tile.
-// fp32 path: one thread per row, K/V tiles staged in LDS, exact fp32 online softmax.
+// The fp32 path is in attention_f32.hip.
 #include <type_traits>
 
 #include "cc_internal.h"
@@ -531,97 +531,7 @@ __global__ __launch_bounds__(256, 2) void attn_cc_bf16(AttnArgs a) {
   }
 }
 
-// ------------------------------------------------------------------ fp32 path
-
-constexpr int F_ROWS = 128;   // rows (one per thread) per workgroup
-constexpr int F_BN = 32;      // keys per LDS tile
-
-struct AttnArgsF {
-  const float* q;
-  float* o;
-  const int32_t* cu;
-  const int4* work;   // null for one sequence: item i is (0, i % nkv, i / nkv)
-  KvView k, v;
-  int layer;
-  int hq, g, nkv;
-  float scale;
-  int inclusive;
-};
-
-template <int D, bool PAGED>
-__global__ __launch_bounds__(F_ROWS) void attn_cc_f32(AttnArgsF a) {
-  __shared__ float Ks[F_BN][D + 1];
-  __shared__ float Vs[F_BN][D + 1];
-  // work item: from the table, or for one sequence from the block index (row blocks in
-  // increasing order, heaviest first, KV heads fastest: the table's order)
-  const int4 w = a.work ? a.work[blockIdx.x]
-                        : make_int4(0, int(blockIdx.x) % a.nkv, int(blockIdx.x) / a.nkv, 0);
-  const int b = w.x, kvh = w.y, rb = w.z;
-  const int seq0 = a.cu[b];
-  const int n = a.cu[b + 1] - seq0;
-  const int g = a.g;
-  const int nrows = n * g;
-  const int row = rb * F_ROWS + threadIdx.x;
-  const bool valid = row < nrows;
-  const int pos = valid ? row / g : n;
-  const int hq = kvh * g + (valid ? row % g : 0);
-
-  float q[D], o[D];
-  const float* qp = a.q + (int64_t(seq0 + (valid ? pos : 0)) * a.hq + hq) * D;
-#pragma unroll
-  for (int e = 0; e < D; ++e) {
-    q[e] = valid ? qp[e] : 0.f;
-    o[e] = 0.f;
-  }
-  float m = -INFINITY, l = 0.f;
-  const int pos_lo = (rb * F_ROWS) / g;
-  const int first = pos_lo + (a.inclusive ? 0 : 1);
-  const int t_begin = first / F_BN;
-  const int t_end = (n + F_BN - 1) / F_BN;
-  const float* kb = reinterpret_cast<const float*>(a.k.base);
-  const float* vb = reinterpret_cast<const float*>(a.v.base);
-
-  for (int t = t_begin; t < t_end; ++t) {
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < F_BN * D; idx += F_ROWS) {
-      const int r = idx / D, e = idx % D;
-      const int key = t * F_BN + r;
-      float kv = 0.f, vv = 0.f;
-      if (key < n) {
-        kv = kb[kv_off<PAGED>(a.k, b, a.layer, kvh, key) + e];
-        vv = vb[kv_off<PAGED>(a.v, b, a.layer, kvh, key) + e];
-      }
-      Ks[r][e] = kv;
-      Vs[r][e] = vv;
-    }
-    __syncthreads();
-    for (int r = 0; r < F_BN; ++r) {
-      const int key = t * F_BN + r;
-      const bool ok = key < n && (a.inclusive ? key >= pos : key > pos);
-      if (!ok) continue;
-      float dot = 0.f;
-#pragma unroll
-      for (int e = 0; e < D; ++e) dot = fmaf(q[e], Ks[r][e], dot);
-      const float sc = dot * a.scale;
-      const float m_new = fmaxf(m, sc);
-      const float corr = expf(m - m_new);
-      const float p = expf(sc - m_new);
-      l = l * corr + p;
-#pragma unroll
-      for (int e = 0; e < D; ++e) o[e] = fmaf(p, Vs[r][e], o[e] * corr);
-      m = m_new;
-    }
-  }
-  if (valid) {
-    const float inv = l > 0.f ? 1.f / l : 0.f;
-    float* op = a.o + (int64_t(seq0 + pos) * a.hq + hq) * D;
-#pragma unroll
-    for (int e = 0; e < D; ++e) op[e] = o[e] * inv;
-  }
-}
-
-template <class Args>
-void fill_common(Args& x, const AttnLaunch& a) {
+void fill_common(AttnArgs& x, const AttnLaunch& a) {
   x.cu = a.cu_d;
   x.work = a.work_d;
   x.k = a.k;
@@ -637,7 +547,7 @@ void fill_common(Args& x, const AttnLaunch& a) {
 
 int attention_rows_per_item(int dtype, int head_dim) {
   (void)head_dim;
-  return dtype == CC_BF16 ? ROWS : F_ROWS;
+  return dtype == CC_BF16 ? ROWS : attention_f32_rows();
 }
 
 hipError_t launch_attention(const AttnLaunch& a, hipStream_t s) {
@@ -661,23 +571,7 @@ hipError_t launch_attention(const AttnLaunch& a, hipStream_t s) {
     }
     return hipGetLastError();
   }
-  AttnArgsF x;
-  fill_common(x, a);
-  x.q = static_cast<const float*>(a.q);
-  x.o = static_cast<float*>(a.o);
-  x.scale = a.scale;
-  if (a.head_dim == 64) {
-    if (a.paged)
-      hipLaunchKernelGGL((attn_cc_f32<64, true>), dim3(a.n_work), dim3(F_ROWS), 0, s, x);
-    else
-      hipLaunchKernelGGL((attn_cc_f32<64, false>), dim3(a.n_work), dim3(F_ROWS), 0, s, x);
-  } else {
-    if (a.paged)
-      hipLaunchKernelGGL((attn_cc_f32<128, true>), dim3(a.n_work), dim3(F_ROWS), 0, s, x);
-    else
-      hipLaunchKernelGGL((attn_cc_f32<128, false>), dim3(a.n_work), dim3(F_ROWS), 0, s, x);
-  }
-  return hipGetLastError();
+  return launch_attention_f32(a, s);
 }
 
 }  // namespace cc

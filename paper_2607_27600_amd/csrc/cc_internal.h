@@ -86,6 +86,9 @@ struct AttnLaunch {
 // Rows per attention work item for the given dtype / head_dim.
 int attention_rows_per_item(int dtype, int head_dim);
 hipError_t launch_attention(const AttnLaunch& a, hipStream_t s);
+// The CC_F32 part of the two above.
+int attention_f32_rows();
+hipError_t launch_attention_f32(const AttnLaunch& a, hipStream_t s);
 
 // GEMM y[M][N] = x[M][K] w[N][K]^T, bf16 in / bf16 out (or f32 for dtype CC_F32).
 hipError_t launch_linear(int dtype, const void* x, const void* w, void* y, int M, int N, int K,
@@ -121,6 +124,12 @@ size_t packed_rows_bytes(int64_t rows, int cols);
 hipError_t launch_pack_rows(const void* x, int64_t rows, int cols, int64_t ldx, void* out,
                             hipStream_t s);
 hipError_t launch_lmhead(const LmHeadLaunch& a, hipStream_t s);
+// The CC_F32 parts of launch_linear and launch_lmhead (its partials and targets; the
+// vocabulary rows per tile).
+hipError_t launch_linear_f32(const float* x, const float* w, float* y, int M, int N, int K,
+                             hipStream_t s);
+hipError_t launch_lmhead_f32(const LmHeadLaunch& a, hipStream_t s);
+int lmhead_f32_vocab_tile();
 
 // FP8 LM head: u (dtype) quantized per row into uq / su, then the E4M3 GEMM with the LSE
 // epilogue on the scaled logits, the target logits and the combine.

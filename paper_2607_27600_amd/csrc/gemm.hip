@@ -14,7 +14,7 @@
 // lane holds 64 logits of one entry and the reduction over the vocabulary is mostly
 // in-lane.  Tiles are rasterised entry-tile-fastest so consecutive workgroups share one
 // LM-head tile.
-// fp32 kernel: a plain LDS-tiled FMA GEMM with the same two epilogues.
+// The fp32 kernels are in gemm_f32.hip.
 #include <algorithm>
 #include <type_traits>
 
@@ -1051,103 +1051,6 @@ __global__ __launch_bounds__(256) void quantize_matrix_kernel(const T* __restric
   quantize_row<T>(x + r * cols, cols, amax[0], q + r * cols);
 }
 
-// ------------------------------------------------------------------ fp32 path
-
-constexpr int FT = 64, FK = 16;
-
-struct GemmArgsF {
-  const float* A;
-  const float* B;
-  int M, N, K;
-  int64_t lda, ldb;
-  int tiles_n;
-};
-
-struct EpiStoreF {
-  float* out;
-  int64_t ldo;
-  __device__ void operator()(const float (&c)[4][4], const GemmArgsF& g, int tm, int m0, int n0,
-                             float* lds) const {
-    (void)tm;
-    (void)lds;
-    const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
-        if (m < g.M && n < g.N) out[int64_t(m) * ldo + n] = c[i][j];
-      }
-  }
-};
-
-struct EpiLseF {
-  float2* partial;
-  float* target;
-  const int32_t* ids;
-  __device__ void operator()(const float (&c)[4][4], const GemmArgsF& g, int tm, int m0, int n0,
-                             float* lds) const {
-    const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;
-    float* T = lds;   // [FT][FT + 1], T[m][n]
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) T[(ty * 4 + i) * (FT + 1) + tx * 4 + j] = c[i][j];
-    __syncthreads();
-    if (threadIdx.x < FT) {
-      const int nl = threadIdx.x, n = n0 + nl;
-      if (n < g.N) {
-        const int id = ids[n];
-        float mx = -INFINITY;
-        for (int ml = 0; ml < FT && m0 + ml < g.M; ++ml) {
-          const float z = T[ml * (FT + 1) + nl];
-          mx = fmaxf(mx, z);
-          if (m0 + ml == id) target[n] = z;
-        }
-        float s = 0.f;
-        for (int ml = 0; ml < FT && m0 + ml < g.M; ++ml) s += expf(T[ml * (FT + 1) + nl] - mx);
-        partial[int64_t(tm) * g.N + n] = make_float2(mx, s);
-      }
-    }
-  }
-};
-
-template <class Epi>
-__global__ __launch_bounds__(256) void gemm_tn_f32(GemmArgsF g, Epi epi) {
-  __shared__ float lds[FT * (FT + 1)];
-  float* As = lds;                 // [FK][FT + 4]
-  float* Bs = lds + FK * (FT + 4); // [FK][FT + 4]
-  const int tm = blockIdx.x / g.tiles_n, tn = blockIdx.x % g.tiles_n;
-  const int m0 = tm * FT, n0 = tn * FT;
-  const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;
-  float c[4][4] = {};
-  for (int k0 = 0; k0 < g.K; k0 += FK) {
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < FT * FK; idx += 256) {
-      const int r = idx / FK, kk = idx % FK;
-      const int m = m0 + r, n = n0 + r, k = k0 + kk;
-      As[kk * (FT + 4) + r] = (m < g.M && k < g.K) ? g.A[int64_t(m) * g.lda + k] : 0.f;
-      Bs[kk * (FT + 4) + r] = (n < g.N && k < g.K) ? g.B[int64_t(n) * g.ldb + k] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < FK; ++kk) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        a[i] = As[kk * (FT + 4) + ty * 4 + i];
-        b[i] = Bs[kk * (FT + 4) + tx * 4 + i];
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) c[i][j] = fmaf(a[i], b[j], c[i][j]);
-    }
-  }
-  epi(c, g, tm, m0, n0, lds);
-}
-
 // ------------------------------------------------------------------ LSE combine
 
 // One workgroup per 16 entries: thread (group gi, entry e) folds the vocabulary tiles
@@ -1255,7 +1158,7 @@ hipError_t launch_transpose(int dtype, const void* in, void* out, int rows, int 
   return hipGetLastError();
 }
 
-int lmhead_vocab_tile(int dtype) { return dtype == CC_BF16 ? GBM : FT; }
+int lmhead_vocab_tile(int dtype) { return dtype == CC_BF16 ? GBM : lmhead_f32_vocab_tile(); }
 
 hipError_t launch_linear(int dtype, const void* x, const void* w, void* y, int M, int N, int K,
                          hipStream_t s) {
@@ -1277,19 +1180,8 @@ hipError_t launch_linear(int dtype, const void* x, const void* w, void* y, int M
     hipLaunchKernelGGL(gemm_tn_bf16<EpiStore>, dim3(tiles), dim3(GNT), 0, s, g, e);
     return hipGetLastError();
   }
-  GemmArgsF g;
-  g.A = static_cast<const float*>(x);
-  g.B = static_cast<const float*>(w);
-  g.M = M;
-  g.N = N;
-  g.K = K;
-  g.lda = K;
-  g.ldb = K;
-  g.tiles_n = (N + FT - 1) / FT;
-  const int tiles = ((M + FT - 1) / FT) * g.tiles_n;
-  EpiStoreF e{static_cast<float*>(y), N};
-  hipLaunchKernelGGL(gemm_tn_f32<EpiStoreF>, dim3(tiles), dim3(256), 0, s, g, e);
-  return hipGetLastError();
+  return launch_linear_f32(static_cast<const float*>(x), static_cast<const float*>(w),
+                           static_cast<float*>(y), M, N, K, s);
 }
 
 size_t packed_rows_bytes(int64_t rows, int cols) {
@@ -1342,18 +1234,9 @@ hipError_t launch_lmhead(const LmHeadLaunch& a, hipStream_t s) {
     EpiLse e{a.partial, a.target, a.ids};
     hipLaunchKernelGGL(gemm_tn_bf16<EpiLse>, dim3(n_vt * g.tiles_n), dim3(GNT), 0, s, g, e);
   } else {
-    GemmArgsF g;
-    g.A = static_cast<const float*>(a.w_lm);
-    g.B = static_cast<const float*>(a.u);
-    g.M = a.V;
-    g.N = a.N;
-    g.K = a.D;
-    g.lda = a.D;
-    g.ldb = a.D;
-    g.tiles_n = (a.N + FT - 1) / FT;
-    n_vt = (a.V + FT - 1) / FT;
-    EpiLseF e{a.partial, a.target, a.ids};
-    hipLaunchKernelGGL(gemm_tn_f32<EpiLseF>, dim3(n_vt * g.tiles_n), dim3(256), 0, s, g, e);
+    n_vt = (a.V + lmhead_f32_vocab_tile() - 1) / lmhead_f32_vocab_tile();
+    hipError_t err = launch_lmhead_f32(a, s);
+    if (err != hipSuccess) return err;
   }
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
