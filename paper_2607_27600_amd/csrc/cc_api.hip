@@ -208,7 +208,6 @@ FullLayout full_layout(const cc_problem* p) {
     const int S = gemm_split_slices(M, Nn, K);
     if (S > 1) part = std::max(part, size_t(S) * size_t(M) * size_t(Nn) * sizeof(float));
   };
-  need(hd, int(N), D);   // W_q
   need(int(N), D, hd);   // W_o
   need(int(N), D, F);    // W_down
   L.part = off;
@@ -351,17 +350,16 @@ cc_status score_full(const cc_problem* p, const cc_inputs* in, float* scores, vo
   CC_HIP(launch_rope_table(in->pos_ids, p->cu_seqlens_d, p->n_seqs, rot, N, p->head_dim,
                            double(p->rope_theta), s));
   CC_HIP(launch_embed(in->embed, in->token_ids, h, N, D, s));
+  CC_HIP(launch_residual_rmsnorm(nullptr, 0, h, in->layers_h[0].attn_norm, a, N, D, p->rms_eps, s));
   for (int l = 0; l < p->n_layers; ++l) {
     const cc_layer_weights& W = in->layers_h[l];
-    CC_HIP(launch_rmsnorm(h, W.attn_norm, a, N, D, p->rms_eps, s));
-    CC_HIP(launch_qproj_rope(W.wq, a, q, rot, N, D, HD, part, s));
+    const void* next = l + 1 < p->n_layers ? in->layers_h[l + 1].attn_norm : in->final_norm;
+    CC_HIP(launch_qproj_rope(W.wq, a, q, rot, N, D, HD, s));
     CC_TRY(run_attention(p, q, &in->kv, l, o, at(ws, L.attn), s, l == 0));
-    CC_HIP(launch_linear_residual(o, W.wo, h, N, D, HD, part, s));
-    CC_HIP(launch_rmsnorm(h, W.mlp_norm, a, N, D, p->rms_eps, s));
+    CC_HIP(launch_linear_residual_norm(o, W.wo, h, W.mlp_norm, a, N, D, HD, p->rms_eps, part, s));
     CC_HIP(launch_gate_up_swiglu(W.w_gate, W.w_up, a, act, N, D, F, s));
-    CC_HIP(launch_linear_residual(act, W.w_down, h, N, D, F, part, s));
+    CC_HIP(launch_linear_residual_norm(act, W.w_down, h, next, a, N, D, F, p->rms_eps, part, s));
   }
-  CC_HIP(launch_rmsnorm(h, in->final_norm, a, N, D, p->rms_eps, s));
   return run_lmhead(p, a, in->w_lm, in->token_ids, scores, nullptr, at(ws, L.lm), s, 0,
                     in->w_lm_packed);
 }
@@ -400,14 +398,12 @@ cc_status score_last_h(const cc_problem* p, const cc_inputs* in, float* scores, 
   CC_HIP(launch_rope_table(in->pos_ids, p->cu_seqlens_d, p->n_seqs, rot, N, p->head_dim,
                            double(p->rope_theta), s));
   CC_HIP(launch_embed(in->h_last, nullptr, h, N, D, s));   // widen H to the fp32 stream
-  CC_HIP(launch_rmsnorm(h, W.attn_norm, a, N, D, p->rms_eps, s));
-  CC_HIP(launch_qproj_rope(W.wq, a, q, rot, N, D, HD, part, s));
+  CC_HIP(launch_residual_rmsnorm(nullptr, 0, h, W.attn_norm, a, N, D, p->rms_eps, s));
+  CC_HIP(launch_qproj_rope(W.wq, a, q, rot, N, D, HD, s));
   CC_TRY(run_attention(p, q, &in->kv, in->kv.n_layers - 1, o, at(ws, L.attn), s));
-  CC_HIP(launch_linear_residual(o, W.wo, h, N, D, HD, part, s));
-  CC_HIP(launch_rmsnorm(h, W.mlp_norm, a, N, D, p->rms_eps, s));
+  CC_HIP(launch_linear_residual_norm(o, W.wo, h, W.mlp_norm, a, N, D, HD, p->rms_eps, part, s));
   CC_HIP(launch_gate_up_swiglu(W.w_gate, W.w_up, a, act, N, D, F, s));
-  CC_HIP(launch_linear_residual(act, W.w_down, h, N, D, F, part, s));
-  CC_HIP(launch_rmsnorm(h, in->final_norm, a, N, D, p->rms_eps, s));
+  CC_HIP(launch_linear_residual_norm(act, W.w_down, h, in->final_norm, a, N, D, F, p->rms_eps, part, s));
   return run_lmhead(p, a, in->w_lm, in->token_ids, scores, nullptr, at(ws, L.lm), s, 0,
                     in->w_lm_packed);
 }

@@ -211,27 +211,27 @@ struct CompactLaunch {
 hipError_t launch_compact(const CompactLaunch& a, hipStream_t s);
 
 // FULL-mode building blocks (bf16, head_dim 128).
-// Split-K: slices a [M][K] x [N][K] product is cut into along K when its 256 x 256 tiles
-// would fill under half the chip (1: one pass).  A split product needs a workspace of
-// slices * M * N floats for its partial sums.
+// Slices that the projection of M entries to N features is cut into along K (1: one pass).  A
+// split product needs a workspace of slices * M * N floats for its partial sums.
 int gemm_split_slices(int M, int N, int K);
 // q[n][:] = RoPE(W_q a[n]) with rot[n][e] = (cos, sin) of the entry's rotation angle.
-// part: gemm_split_slices(HD, N, D) * N * HD floats when that count exceeds 1, else unused.
 hipError_t launch_qproj_rope(const void* wq, const void* a, void* q, const float2* rot, int N,
-                             int D, int HD, float* part, hipStream_t s);
-// h[m][:] += x[m][:] W^T (fp32 residual stream).
+                             int D, int HD, hipStream_t s);
+// h[m][:] += x[m][:] W^T (fp32 residual stream), then y = RMSNorm(h) with gain gamma.
 // part: gemm_split_slices(M, N, K) * M * N floats when that count exceeds 1, else unused.
-hipError_t launch_linear_residual(const void* x, const void* w, float* h, int M, int N, int K,
-                                  float* part, hipStream_t s);
+hipError_t launch_linear_residual_norm(const void* x, const void* w, float* h, const void* gamma,
+                                       void* y, int M, int N, int K, float eps, float* part,
+                                       hipStream_t s);
 // act[n][f] = silu(W_gate b[n])[f] * (W_up b[n])[f].
 hipError_t launch_gate_up_swiglu(const void* w_gate, const void* w_up, const void* b, void* act,
                                  int N, int D, int F, hipStream_t s);
 // h[n][:] = embed[ids[n]][:] (bf16 -> fp32); ids == null widens row n of `embed`.
 hipError_t launch_embed(const void* embed, const int32_t* ids, float* h, int N, int D,
                         hipStream_t s);
-// y[n][:] = bf16(h[n][:] / sqrt(mean(h[n]^2) + eps) * gamma).
-hipError_t launch_rmsnorm(const float* h, const void* gamma, void* y, int N, int D, float eps,
-                          hipStream_t s);
+// y[n][:] = bf16(h[n][:] / sqrt(mean(h[n]^2) + eps) * gamma), after h += part[0] + ... +
+// part[S-1] (each [N][D]) when part is not null.
+hipError_t launch_residual_rmsnorm(const float* part, int S, float* h, const void* gamma, void* y,
+                                   int N, int D, float eps, hipStream_t s);
 // rot[n][e] = (cos, sin)(pos[n] * theta^(-2e/head_dim)), e < head_dim/2, computed in fp64.
 // pos == null: positions 0..n_b-1 within each sequence.
 hipError_t launch_rope_table(const int32_t* pos, const int32_t* cu, int n_seqs, float2* rot,

@@ -1160,30 +1160,6 @@ hipError_t launch_transpose(int dtype, const void* in, void* out, int rows, int 
 
 int lmhead_vocab_tile(int dtype) { return dtype == CC_BF16 ? GBM : lmhead_f32_vocab_tile(); }
 
-hipError_t launch_linear(int dtype, const void* x, const void* w, void* y, int M, int N, int K,
-                         hipStream_t s) {
-  if (M == 0 || N == 0) return hipSuccess;
-  if (dtype == CC_BF16) {
-    GemmArgs g;
-    g.A2 = nullptr;
-    g.A = static_cast<const u16*>(x);
-    g.B = static_cast<const u16*>(w);
-    g.M = M;
-    g.N = N;
-    g.K = K;
-    g.lda = K;
-    g.ldb = K;
-    g.tiles_n = (N + GBN - 1) / GBN;
-    g.tiles_m = (M + GBM - 1) / GBM;
-    const int tiles = g.tiles_m * g.tiles_n;
-    EpiStore e{static_cast<u16*>(y), N};
-    hipLaunchKernelGGL(gemm_tn_bf16<EpiStore>, dim3(tiles), dim3(GNT), 0, s, g, e);
-    return hipGetLastError();
-  }
-  return launch_linear_f32(static_cast<const float*>(x), static_cast<const float*>(w),
-                           static_cast<float*>(y), M, N, K, s);
-}
-
 size_t packed_rows_bytes(int64_t rows, int cols) {
   return size_t((rows + PK_ROWS - 1) / PK_ROWS) * PK_ROWS * size_t(cols) * 2;
 }
@@ -1297,99 +1273,6 @@ hipError_t launch_lmhead_fp8(const LmHeadFp8Launch& a, hipStream_t s) {
   hipLaunchKernelGGL(lse_combine, dim3((a.N + CMB_E - 1) / CMB_E), dim3(CMB_E * CMB_G), 0, s,
                      a.partial, n_vt, a.target, a.cu_d, a.n_seqs, a.n_frozen, a.N, a.scores,
                      a.lse);
-  return hipGetLastError();
-}
-
-namespace {
-GemmArgs make_args(const void* a, const void* b, int M, int N, int K, int64_t lda, int64_t ldb) {
-  GemmArgs g;
-  g.A = static_cast<const u16*>(a);
-  g.B = static_cast<const u16*>(b);
-  g.A2 = nullptr;
-  g.M = M;
-  g.N = N;
-  g.K = K;
-  g.lda = lda;
-  g.ldb = ldb;
-  g.tiles_m = (M + GBM - 1) / GBM;
-  g.tiles_n = (N + GBN - 1) / GBN;
-  return g;
-}
-}  // namespace
-
-int gemm_split_slices(int M, int N, int K) {
-  const int tiles = ((M + GBM - 1) / GBM) * ((N + GBN - 1) / GBN);
-  const int nk = K / GBK;
-  if (tiles >= 128 || nk < 8) return 1;
-  // up to one workgroup per CU, at least four k-tiles per slice, at most 5 slices: more
-  // slices add partial sums to write and reduce faster than they add parallelism (measured at
-  // 42 tiles, 768 entries: 3, 4, 5 and 7 slices give 1.28, 1.26, 1.25 and 1.31 ms per refresh)
-  const int want = std::max(1, std::min({(256 + tiles - 1) / tiles, nk / 4, 5}));
-  const int per = (nk + want - 1) / want;
-  return (nk + per - 1) / per;
-}
-
-namespace {
-// k-tiles per slice for the slice count gemm_split_slices chose
-int split_ktiles(int K, int S) {
-  const int nk = K / GBK;
-  return (nk + S - 1) / S;
-}
-}  // namespace
-
-hipError_t launch_qproj_rope(const void* wq, const void* a, void* q, const float2* rot, int N,
-                             int D, int HD, float* part, hipStream_t s) {
-  if (N == 0) return hipSuccess;
-  GemmArgs g = make_args(wq, a, HD, N, D, D, D);
-  const int S = gemm_split_slices(HD, N, D);
-  if (S > 1) {
-    g.kt_split = split_ktiles(D, S);
-    EpiPartial<true> e{part};
-    hipLaunchKernelGGL(gemm_tn_bf16<EpiPartial<true>>, dim3(g.tiles_m * g.tiles_n, S), dim3(GNT),
-                       0, s, g, e);
-    hipError_t err = hipGetLastError();
-    if (err != hipSuccess) return err;
-    const int64_t threads = int64_t(N) * (HD / 2);
-    hipLaunchKernelGGL(reduce_rope, dim3(unsigned((threads + 255) / 256)), dim3(256), 0, s, part,
-                       S, N, HD, rot, static_cast<u16*>(q));
-    return hipGetLastError();
-  }
-  EpiRope e{static_cast<u16*>(q), rot};
-  hipLaunchKernelGGL(gemm_tn_bf16<EpiRope>, dim3(g.tiles_m * g.tiles_n), dim3(GNT), 0, s, g, e);
-  return hipGetLastError();
-}
-
-hipError_t launch_linear_residual(const void* x, const void* w, float* h, int M, int N, int K,
-                                  float* part, hipStream_t s) {
-  if (M == 0) return hipSuccess;
-  GemmArgs g = make_args(x, w, M, N, K, K, K);
-  const int S = gemm_split_slices(M, N, K);
-  if (S > 1) {
-    g.kt_split = split_ktiles(K, S);
-    EpiPartial<false> e{part};
-    hipLaunchKernelGGL(gemm_tn_bf16<EpiPartial<false>>, dim3(g.tiles_m * g.tiles_n, S),
-                       dim3(GNT), 0, s, g, e);
-    hipError_t err = hipGetLastError();
-    if (err != hipSuccess) return err;
-    const int64_t count = int64_t(M) * N;
-    hipLaunchKernelGGL(reduce_residual, dim3(unsigned((count / 4 + 255) / 256)), dim3(256), 0, s,
-                       part, S, count, h);
-    return hipGetLastError();
-  }
-  EpiResidual e{h};
-  hipLaunchKernelGGL(gemm_tn_bf16<EpiResidual>, dim3(g.tiles_m * g.tiles_n), dim3(GNT), 0, s, g,
-                     e);
-  return hipGetLastError();
-}
-
-hipError_t launch_gate_up_swiglu(const void* w_gate, const void* w_up, const void* b, void* act,
-                                 int N, int D, int F, hipStream_t s) {
-  if (N == 0) return hipSuccess;
-  GemmArgs g = make_args(w_gate, b, 2 * F, N, D, D, D);
-  g.A2 = static_cast<const u16*>(w_up);
-  EpiSwiglu e{static_cast<u16*>(act), F};
-  hipLaunchKernelGGL((gemm_tn_bf16<EpiSwiglu, true>), dim3(g.tiles_m * g.tiles_n), dim3(GNT), 0,
-                     s, g, e);
   return hipGetLastError();
 }
 
