@@ -201,7 +201,7 @@ def lmhead_traffic(cfg_name: str):
     or None when there is none or the GEMM source has changed since it was taken."""
     import hashlib
     path = os.path.join(ROOT, "profiles", f"lmhead_{cfg_name.lower()}_traffic.json")
-    src = os.path.join(ROOT, "paper_2607_27600_amd", "csrc", "gemm.hip")
+    src = os.path.join(ROOT, "paper_2607_27600_amd", "csrc", "gemm_tile.h")
     try:
         with open(path) as f:
             rec = json.load(f)
@@ -428,7 +428,7 @@ def bench_config(args, name: str, dev, with_extras: bool) -> dict:
         lm_tflops = lm_flop / (part["lmhead_lse"] * 1e-3) / 1e12
         res["roofline"] = {
             "kernel": "LM head on packed operands with the fused log-sum-exp and target gather "
-                      "(pack_rows of U + gemm_lmhead_packed<EpiLse16> + lse_combine)",
+                      "(gemm_tile<8, 4, 3, 2, A_PACKED, EpiLse> + lse_combine)",
             "bound": "mfma", "achieved": lm_tflops, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
             "frac": lm_tflops / PEAK_BF16_TFLOPS, "traffic": lmhead_traffic(name),
             "flop_per_launch": lm_flop}

@@ -134,9 +134,8 @@ typedef struct cc_problem {
   int32_t n_frozen;            /* first n_frozen entries of each sequence are sink
                                   slots that are never evicted (score +inf) */
   int32_t lmhead_packed;       /* bf16 only: 1 = the LM head reads the packed weight
-                                  cc_inputs.w_lm_packed (cc_pack_lmhead) and packs its
-                                  input rows in the workspace (cc_inputs.w_lm is then
-                                  not read and may be NULL); 0 = row-major w_lm */
+                                  cc_inputs.w_lm_packed (cc_pack_lmhead; cc_inputs.w_lm
+                                  is then not read and may be NULL); 0 = row-major w_lm */
 } cc_problem;
 
 /* Weights of one transformer layer (FULL, LAST_LAYER_H), device pointers in `dtype`. */
@@ -292,16 +291,14 @@ cc_status cc_pack_lmhead_bytes(int64_t rows, int32_t cols, size_t* bytes);
  * and 32-column step, one 16 KB block in which row r (64 bytes at 64r) holds its
  * 16-byte chunk c (columns 8c .. 8c+7 of the step) at chunk position c ^ ((r >> 1) & 3);
  * rows past `rows` are zero.  A bit copy that changes the layout only: the weight
- * preparation for lmhead_packed = 1, made once per model (the LM-head input rows are
- * packed inside each call).  out: device, cc_pack_lmhead_bytes bytes, 16-byte aligned,
+ * preparation for lmhead_packed = 1, made once per model.  out: device, cc_pack_lmhead_bytes bytes, 16-byte aligned,
  * not overlapping x. */
 cc_status cc_pack_lmhead(const void* x, int64_t rows, int32_t cols, void* out,
                          size_t out_bytes, void* stream);
 
 /* cc_lmhead_score with p->lmhead_packed = 1: w_packed is w_lm [V][D] packed by
  * cc_pack_lmhead (the row-major weight is not needed).  The result equals
- * cc_lmhead_score up to fp32 summation order (the packed kernel accumulates in another
- * order on the 16x16x32 matrix-core shape).  Workspace: cc_lmhead_workspace(p). */
+ * cc_lmhead_score (the same sums on another layout of the weight).  Workspace: cc_lmhead_workspace(p). */
 cc_status cc_lmhead_score_packed(const cc_problem* p, const void* u, const void* w_packed,
                                  const int32_t* token_ids, float* scores, float* lse,
                                  void* workspace, size_t workspace_bytes, void* stream);

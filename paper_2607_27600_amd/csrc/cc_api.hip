@@ -156,20 +156,12 @@ size_t attention_ws_bytes(const cc_problem* p) {
   return align_up(items * sizeof(int4));
 }
 
-// Input width of the LM head: the model width, or Hq*d for the W_o-folded weight.
-int lmhead_k(const cc_problem* p) {
-  return p->mode == CC_MODE_LAST_LAYER_FUSED ? p->n_heads_q * p->head_dim : p->hidden;
-}
-
-// LM-head workspace: per-(vocabulary tile, entry) partials, target logits and, for the
-// packed LM head, the packed input rows.
+// LM-head workspace: per-(vocabulary tile, entry) partials and target logits.
 size_t lmhead_ws_bytes(const cc_problem* p) {
   const size_t N = n_tokens(p);
   const int vt = lmhead_vocab_tile(p->dtype);
   const size_t n_vt = (p->vocab + vt - 1) / vt;
-  size_t b = align_up(n_vt * N * sizeof(float2)) + align_up(N * sizeof(float));
-  if (p->lmhead_packed) b += align_up(packed_rows_bytes(int64_t(N), lmhead_k(p)));
-  return b;
+  return align_up(n_vt * N * sizeof(float2)) + align_up(N * sizeof(float));
 }
 
 struct ScoreLayout {
@@ -290,7 +282,6 @@ cc_status run_lmhead(const cc_problem* p, const void* u, const void* w_lm, const
   if (p->lmhead_packed) {
     if (!w_packed) return CC_ERR_ARG;
     a.w_packed = w_packed;
-    a.u_packed = at(ws, align_up(n_vt * N * sizeof(float2)) + align_up(N * sizeof(float)));
   }
   CC_HIP(launch_lmhead(a, s));
   return CC_OK;

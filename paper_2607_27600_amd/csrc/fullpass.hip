@@ -1,7 +1,7 @@
 // Elementwise steps of the full counter-causal pass (Sec. 3.1: every layer runs with fresh
 // queries at the original position ids against the stored keys/values): the embedding
 // gather into the fp32 residual stream, RMSNorm to the bf16 GEMM input, and the rotary
-// angle table.  The GEMMs (with RoPE / residual / SwiGLU epilogues) live in gemm.hip.
+// angle table.  The GEMMs (with RoPE / residual / SwiGLU epilogues) live in projections.hip.
 #include "cc_internal.h"
 
 namespace cc {

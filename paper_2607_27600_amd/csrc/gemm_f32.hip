@@ -1,5 +1,5 @@
 // fp32 contractions of the scoring pass (CC_F32 problems): y = x W^T and the LM head with
-// its log-sum-exp reduced on the fly, as in gemm.hip, on the 16x16x4 fp32 MFMA (plain fp32
+// its log-sum-exp reduced on the fly, as in lmhead.hip, on the 16x16x4 fp32 MFMA (plain fp32
 // multiply-adds, twice the rate of the vector ALUs).
 //
 // C[m][n] = sum_k A[m][k] B[n][k], both operands K-contiguous.  A workgroup of four waves

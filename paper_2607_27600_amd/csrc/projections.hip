@@ -215,6 +215,7 @@ TilePlan plan_tiles(int M, int N, int K, bool may_split) {
 
 template <int AM, template <int, int> class Epi, class... E>
 hipError_t launch_shape(const TilePlan& p, const TileArgs& g, hipStream_t s, E... e) {
+  if (g.K >= kWideRow) return launch_tile<4, 4, 4, 3, AM, true>(g, Epi<4, 4>{e...}, p.slices, s);
   switch (p.shape) {
     case 0: return launch_tile<8, 4, 3, 2, AM>(g, Epi<8, 4>{e...}, p.slices, s);
     case 1: return launch_tile<7, 4, 3, 2, AM>(g, Epi<7, 4>{e...}, p.slices, s);

@@ -16,7 +16,7 @@ issue statistics per kernel: see issue().
 
 FETCH_SIZE / WRITE_SIZE are in KiB per dispatch.  The driver also copies 1 GiB device to
 device; each counter is scaled by (1 GiB / what it reads for that copy), so the figures are
-calibrated against a transfer of known size.  The record carries the sha256 of gemm.hip;
+calibrated against a transfer of known size.  The record carries the sha256 of gemm_tile.h;
 bench.py reports the traffic only while the source matches.
 """
 from __future__ import annotations
@@ -52,7 +52,7 @@ def _find(rows, pred):
 def main(fetch_dir: str, write_dir: str, out: str, cfg_name: str = "C5") -> None:
     f_rows = _per_dispatch(os.path.join(fetch_dir, "run_counter_collection.csv"), "FETCH_SIZE")
     w_rows = _per_dispatch(os.path.join(write_dir, "run_counter_collection.csv"), "WRITE_SIZE")
-    is_lm = lambda n: "gemm_lmhead_packed" in n
+    is_lm = lambda n: "gemm_tile" in n and "EpiLse" in n
     is_copy = lambda n: "copy" in n.lower() and "gemm" not in n and "compact" not in n
     # the copy is the last dispatch of the driver; take the largest copy-like dispatch
     f_copy = max(_find(f_rows, is_copy))
@@ -61,7 +61,7 @@ def main(fetch_dir: str, write_dir: str, out: str, cfg_name: str = "C5") -> None
     w_lm = _find(w_rows, is_lm)[-1]
     kf, kw = GIB_KIB / f_copy, GIB_KIB / w_copy
     here = os.path.dirname(os.path.abspath(__file__))
-    with open(os.path.join(here, "csrc", "gemm.hip"), "rb") as fh:
+    with open(os.path.join(here, "csrc", "gemm_tile.h"), "rb") as fh:
         digest = hashlib.sha256(fh.read()).hexdigest()
     sys.path.insert(0, os.path.dirname(here))
     from synth import configs as C
@@ -70,14 +70,14 @@ def main(fetch_dir: str, write_dir: str, out: str, cfg_name: str = "C5") -> None
     vt = (V + 255) // 256
     alg = 2 * V * D + 2 * N * D + 8 * vt * N + 4 * N
     rec = {
-        "kernel": f"gemm_lmhead_packed<EpiLse16> (LM head on packed operands + fused "
+        "kernel": f"gemm_tile<8, 4, 3, 2, A_PACKED, EpiLse> (LM head on the packed weight + fused "
                   f"log-sum-exp and target gather), {cfg_name} shapes",
         "fetch_kib_raw": f_lm, "write_kib_raw": w_lm,
         "copy_fetch_kib_raw": f_copy, "copy_write_kib_raw": w_copy,
         "fetch_scale": kf, "write_scale": kw,
         "bytes_per_launch": (f_lm * kf + w_lm * kw) * 1024.0,
         "algorithmic_bytes": alg,
-        "algorithmic_bytes_note": f"W_lm {V}x{D} bf16 + U {N}x{D} bf16 read (both packed) + "
+        "algorithmic_bytes_note": f"W_lm {V}x{D} bf16 (packed) + U {N}x{D} bf16 read + "
                                   f"partials {vt}x{N}x8 B and target logits {N}x4 B written",
         "traffic_over_algorithmic": (f_lm * kf + w_lm * kw) * 1024.0 / alg,
         "gemm_source_sha256": digest,
