@@ -156,12 +156,21 @@ size_t attention_ws_bytes(const cc_problem* p) {
   return align_up(items * sizeof(int4));
 }
 
-// LM-head workspace: per-(vocabulary tile, entry) partials and target logits.
+// Input width of the LM head: the model width, or Hq*d for the W_o-folded weight.
+int lmhead_k(const cc_problem* p) {
+  return p->mode == CC_MODE_LAST_LAYER_FUSED ? p->n_heads_q * p->head_dim : p->hidden;
+}
+
+// LM-head workspace: per-(vocabulary tile, entry) partials and target logits.  The size asked
+// of a caller with a packed weight also covers a packed copy of the entry rows; the kernels
+// read the rows as they are, the size is part of the interface.
 size_t lmhead_ws_bytes(const cc_problem* p) {
   const size_t N = n_tokens(p);
   const int vt = lmhead_vocab_tile(p->dtype);
   const size_t n_vt = (p->vocab + vt - 1) / vt;
-  return align_up(n_vt * N * sizeof(float2)) + align_up(N * sizeof(float));
+  size_t b = align_up(n_vt * N * sizeof(float2)) + align_up(N * sizeof(float));
+  if (p->lmhead_packed) b += align_up(packed_rows_bytes(int64_t(N), lmhead_k(p)));
+  return b;
 }
 
 struct ScoreLayout {
