@@ -759,19 +759,57 @@ cc_status cc_select_keep(const float* scores, int32_t n_segs, const int64_t* seg
 // ------------------------------------------------------------------ compaction
 
 namespace {
-struct CompactPlan {
-  std::vector<CompactList> lists;
-  std::vector<CompactPlane> planes;
-  std::vector<int32_t> seq_list;
-  int max_k = 0;
-  size_t off_lists = 0, off_planes = 0, off_seq = 0, total = 0;
-};
-
+// Bytes of the planning tables the compaction was first built with ({seq, layer, head, list}
+// of 16 bytes a plane); the lists, all that is uploaded (when they do not fit the kernel
+// arguments), always fit.  The size is part of the interface.
 size_t compact_ws_bytes_for(const cc_problem* p, int per_head, int n_layers) {
   const size_t n_lists = size_t(p->n_seqs) * (per_head ? p->n_heads_kv : 1);
   const size_t n_planes = size_t(p->n_seqs) * n_layers * p->n_heads_kv;
-  return align_up(n_lists * sizeof(CompactList)) + align_up(n_planes * sizeof(CompactPlane)) +
+  return align_up(n_lists * sizeof(CompactList)) + align_up(n_planes * 16) +
          align_up(size_t(p->n_seqs) * sizeof(int32_t));
+}
+
+// The lists of a compaction in the order the kernels want: sequences by falling budget (of
+// the longest list of each), heads in order.  per: lists a sequence; take: lists kept of them
+// (per, or 1: the first).  Checks the budgets; off: kept entries in all.
+cc_status compact_lists(const cc_problem* p, const int32_t* k_h, int per, int take, bool flat,
+                        std::vector<CompactList>& lists, int& max_k, int64_t& off) {
+  const int B = p->n_seqs;
+  std::vector<CompactList> raw(size_t(B) * take);
+  std::vector<int> most(B, 0), order(B);
+  off = 0;
+  max_k = 0;
+  for (int b = 0; b < B; ++b) {
+    const int n = p->cu_seqlens_h[b + 1] - p->cu_seqlens_h[b];
+    order[b] = b;
+    for (int h = 0; h < per; ++h) {
+      const int k = k_h[int64_t(b) * per + h];
+      if (k < 0 || k > n) return CC_ERR_SHAPE;
+      if (h < take) {
+        raw[size_t(b) * take + h] = CompactList{off, flat ? p->cu_seqlens_h[b] : 0, k, b};
+        most[b] = std::max(most[b], k);
+      }
+      off += k;
+    }
+    max_k = std::max(max_k, most[b]);
+  }
+  std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return most[x] > most[y]; });
+  lists.resize(raw.size());
+  for (int i = 0; i < B; ++i)
+    std::copy_n(raw.begin() + size_t(order[i]) * take, take, lists.begin() + size_t(i) * take);
+  return CC_OK;
+}
+
+// The lists by value with the launch, or uploaded into the workspace.
+cc_status compact_run(CompactLaunch& c, const std::vector<CompactList>& lists, void* ws, hipStream_t s) {
+  c.lists_h = lists.data();
+  c.lists_d = nullptr;
+  if (lists.size() > size_t(COMPACT_INLINE)) {
+    CC_HIP(hipMemcpyAsync(ws, lists.data(), lists.size() * sizeof(CompactList), hipMemcpyHostToDevice, s));
+    c.lists_d = static_cast<const CompactList*>(ws);
+  }
+  CC_HIP(launch_compact(c, s));
+  return CC_OK;
 }
 }  // namespace
 
@@ -801,56 +839,14 @@ cc_status cc_compact_kv(const cc_problem* p, const cc_kv* kv, const int32_t* kee
   const int row_bytes = p->head_dim * es;
   if (row_bytes % 16 != 0 || !is_pow2(row_bytes / 16) || row_bytes / 16 > 256)
     return CC_ERR_UNSUPPORTED;
-  const int hkv = p->n_heads_kv;
-  const int n_lists = p->n_seqs * (per_head ? hkv : 1);
-  CompactPlan plan;
-  plan.lists.resize(n_lists);
+  const int hkv = p->n_heads_kv, per = per_head ? hkv : 1;
+  std::vector<CompactList> lists;
+  int max_k = 0;
   int64_t off = 0;
-  for (int b = 0; b < p->n_seqs; ++b) {
-    const int n = p->cu_seqlens_h[b + 1] - p->cu_seqlens_h[b];
-    for (int h = 0; h < (per_head ? hkv : 1); ++h) {
-      const int li = per_head ? b * hkv + h : b;
-      const int k = k_h[li];
-      if (k < 0 || k > n) return CC_ERR_SHAPE;
-      plan.lists[li].keep_off = off;
-      plan.lists[li].tok0 = 0;
-      plan.lists[li].k = k;
-      plan.lists[li].pad = 0;
-      off += k;
-      plan.max_k = std::max(plan.max_k, k);
-    }
-  }
+  CC_TRY(compact_lists(p, k_h, per, per, false, lists, max_k, off));
   if (off > 0 && !keep_idx) return CC_ERR_ARG;
-  plan.seq_list.resize(p->n_seqs);
-  for (int b = 0; b < p->n_seqs; ++b) plan.seq_list[b] = per_head ? b * hkv : b;
-  const int L = kv->n_layers;
-  for (int b = 0; b < p->n_seqs; ++b)
-    for (int l = 0; l < L; ++l)
-      for (int h = 0; h < hkv; ++h) {
-        const int li = per_head ? b * hkv + h : b;
-        if (plan.lists[li].k == 0) continue;
-        plan.planes.push_back(CompactPlane{b, l, h, li});
-      }
-  std::stable_sort(plan.planes.begin(), plan.planes.end(),
-                   [&](const CompactPlane& a, const CompactPlane& c) {
-                     return plan.lists[a.list].k > plan.lists[c.list].k;
-                   });
-  plan.off_lists = 0;
-  plan.off_planes = align_up(plan.lists.size() * sizeof(CompactList));
-  plan.off_seq = plan.off_planes + align_up(size_t(p->n_seqs) * L * hkv * sizeof(CompactPlane));
-  plan.total = plan.off_seq + align_up(size_t(p->n_seqs) * sizeof(int32_t));
-  if (plan.total != compact_ws_bytes_for(p, per_head, L)) return CC_ERR_ARG;
-  CC_TRY(check_ws(ws, ws_bytes, plan.total));
+  CC_TRY(check_ws(ws, ws_bytes, compact_ws_bytes_for(p, per_head, kv->n_layers)));
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // the three tables go up as one host image of the workspace prefix: one copy, not three
-  // (each copy from pageable memory is a separate transfer on the stream)
-  std::vector<char> img(plan.off_seq + plan.seq_list.size() * sizeof(int32_t));
-  std::memcpy(img.data() + plan.off_lists, plan.lists.data(), plan.lists.size() * sizeof(CompactList));
-  if (!plan.planes.empty())
-    std::memcpy(img.data() + plan.off_planes, plan.planes.data(),
-                plan.planes.size() * sizeof(CompactPlane));
-  std::memcpy(img.data() + plan.off_seq, plan.seq_list.data(), plan.seq_list.size() * sizeof(int32_t));
-  CC_HIP(hipMemcpyAsync(ws, img.data(), img.size(), hipMemcpyHostToDevice, s));
   CompactLaunch c;
   c.n_tensors = 2;
   const cc_kv* dst = out ? out : kv;
@@ -861,18 +857,16 @@ cc_status cc_compact_kv(const cc_problem* p, const cc_kv* kv, const int32_t* kee
   c.paged = kv->layout == CC_KV_PAGED;
   c.row_bytes = row_bytes;
   c.keep = keep_idx;
-  c.lists_d = reinterpret_cast<const CompactList*>(at(ws, plan.off_lists));
-  c.planes_d = reinterpret_cast<const CompactPlane*>(at(ws, plan.off_planes));
-  c.n_planes = int(plan.planes.size());
-  c.max_k = plan.max_k;
+  c.n_seqs = p->n_seqs;
+  c.n_layers = kv->n_layers;
+  c.n_heads = hkv;
+  c.per_head = per_head;
+  c.max_k = max_k;
   c.in_place = out == nullptr;
   c.ids[0] = token_ids;
   c.ids[1] = pos_ids;
   c.cu_d = p->cu_seqlens_d;
-  c.seq_list_d = reinterpret_cast<const int32_t*>(at(ws, plan.off_seq));
-  c.n_seqs = p->n_seqs;
-  CC_HIP(launch_compact(c, s));
-  return CC_OK;
+  return compact_run(c, lists, ws, s);
 }
 
 // Token-major per-entry rows (e.g. the stored activations H) follow the keep lists of
@@ -887,8 +881,7 @@ int rows_slab_bytes(int row_bytes) {
 }
 size_t rows_ws_bytes(const cc_problem* p, int row_bytes) {
   const size_t n_slabs = size_t(row_bytes / rows_slab_bytes(row_bytes));
-  return align_up(size_t(p->n_seqs) * sizeof(CompactList)) +
-         align_up(size_t(p->n_seqs) * n_slabs * sizeof(CompactPlane));
+  return align_up(size_t(p->n_seqs) * sizeof(CompactList)) + align_up(size_t(p->n_seqs) * n_slabs * 16);
 }
 }  // namespace
 
@@ -911,39 +904,15 @@ cc_status cc_compact_rows(const cc_problem* p, void* rows, int32_t row_bytes,
   if (!k_h) return CC_ERR_ARG;
   const int hkv = p->n_heads_kv;
   const int slab = rows_slab_bytes(row_bytes), n_slabs = row_bytes / slab;
-  std::vector<CompactList> lists(p->n_seqs);
-  std::vector<CompactPlane> planes;
-  int64_t off = 0;
+  std::vector<CompactList> lists;
   int max_k = 0;
-  for (int b = 0; b < p->n_seqs; ++b) {
-    const int n = p->cu_seqlens_h[b + 1] - p->cu_seqlens_h[b];
-    for (int h = 0; h < (per_head ? hkv : 1); ++h) {
-      const int li = per_head ? b * hkv + h : b;
-      if (k_h[li] < 0 || k_h[li] > n) return CC_ERR_SHAPE;
-      if (h == 0) {   // the sequence's first list
-        lists[b].keep_off = off;
-        lists[b].tok0 = p->cu_seqlens_h[b];
-        lists[b].k = k_h[li];
-        lists[b].pad = 0;
-        max_k = std::max(max_k, k_h[li]);
-      }
-      off += k_h[li];
-    }
-  }
+  int64_t off = 0;
+  CC_TRY(compact_lists(p, k_h, per_head ? hkv : 1, 1, true, lists, max_k, off));
   if (off > 0 && (!keep_idx || !rows)) return CC_ERR_ARG;
   if ((rows && !aligned16(rows)) || (out_rows && !aligned16(out_rows))) return CC_ERR_ARG;
-  for (int b = 0; b < p->n_seqs; ++b)
-    if (lists[b].k > 0)
-      for (int h = 0; h < n_slabs; ++h) planes.push_back(CompactPlane{b, 0, h, b});
-  const size_t off_planes = align_up(size_t(p->n_seqs) * sizeof(CompactList));
   CC_TRY(check_ws(ws, ws_bytes, rows_ws_bytes(p, row_bytes)));
-  if (planes.empty()) return CC_OK;
+  if (max_k == 0) return CC_OK;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // both tables as one host image of the workspace prefix (one copy)
-  std::vector<char> img(off_planes + planes.size() * sizeof(CompactPlane));
-  std::memcpy(img.data(), lists.data(), lists.size() * sizeof(CompactList));
-  std::memcpy(img.data() + off_planes, planes.data(), planes.size() * sizeof(CompactPlane));
-  CC_HIP(hipMemcpyAsync(ws, img.data(), img.size(), hipMemcpyHostToDevice, s));
   auto view = [&](void* base) {
     KvView v{};
     v.base = base;
@@ -958,17 +927,15 @@ cc_status cc_compact_rows(const cc_problem* p, void* rows, int32_t row_bytes,
   c.paged = false;
   c.row_bytes = slab;
   c.keep = keep_idx;
-  c.lists_d = static_cast<const CompactList*>(ws);
-  c.planes_d = reinterpret_cast<const CompactPlane*>(at(ws, off_planes));
-  c.n_planes = int(planes.size());
+  c.n_seqs = p->n_seqs;
+  c.n_layers = 1;
+  c.n_heads = n_slabs;   // a column slab is a "head" of the flat view
+  c.per_head = 0;
   c.max_k = max_k;
   c.in_place = out_rows == nullptr;
   c.ids[0] = c.ids[1] = nullptr;
   c.cu_d = p->cu_seqlens_d;
-  c.seq_list_d = nullptr;
-  c.n_seqs = 0;
-  CC_HIP(launch_compact(c, s));
-  return CC_OK;
+  return compact_run(c, lists, ws, s);
 }
 
 }  // extern "C"

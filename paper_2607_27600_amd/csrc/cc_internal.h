@@ -178,32 +178,30 @@ bool select_regular(const SelSeg* segs_h, int n_segs);
 hipError_t launch_select(const float* scores, const SelSeg* segs_h, const SelSeg* segs_d,
                          int n_segs, int max_len, int32_t* keep, hipStream_t s);
 
-// KV compaction: one workgroup per (list, layer, head, tensor) plane.
-struct CompactPlane {
-  int32_t seq, layer, head, list;  // list: index into list table
-};
+// KV compaction.  One keep list; the lists of a launch are sorted by falling budget of their
+// sequence (per_head: n_heads lists a sequence, in head order).
 struct CompactList {
   int64_t keep_off;  // offset of the list in keep_idx
   int64_t tok0;      // first row of the sequence in a flat token-major array (0 for caches)
   int32_t k;
-  int32_t pad;
+  int32_t seq;
 };
+// Up to COMPACT_INLINE lists travel by value in the kernel arguments (no upload).
+constexpr int COMPACT_INLINE = 64;
 struct CompactLaunch {
   KvView src[2], dst[2];   // keys, values; strides in BYTES
   int n_tensors;           // 2 (keys and values) or 1
   bool paged;
   int row_bytes;           // head_dim * element size
   const int32_t* keep;
-  const CompactList* lists_d;
-  const CompactPlane* planes_d;
-  int n_planes;            // planes per tensor
+  const CompactList* lists_h;   // host
+  const CompactList* lists_d;   // the same in device memory, null for up to COMPACT_INLINE
+  int n_seqs, n_layers, n_heads, per_head;   // planes: n_seqs * n_layers * n_heads
   int max_k;               // longest list (bounds the out-of-place grid)
   bool in_place;
-  // token/pos ids
+  // token/pos ids, moved in place by the first list of each sequence
   int32_t* ids[2];
   const int32_t* cu_d;
-  const int32_t* seq_list_d;  // list index of each sequence's first list
-  int n_seqs;
 };
 hipError_t launch_compact(const CompactLaunch& a, hipStream_t s);
 

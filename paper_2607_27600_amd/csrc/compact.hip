@@ -10,7 +10,15 @@
 // read of those slots before the writes.  The sources of chunk c+1 are at or past slot
 // (c+1)*rows, beyond everything chunk c writes, so its loads (and the keep indices of
 // chunk c+3) are issued before chunk c is written and stay in flight across the barrier.  A plane is (sequence, layer,
-// KV head, keys|values); there are hundreds to thousands per refresh.
+// KV head, keys|values, column slab); there are hundreds to thousands per refresh.
+//
+// A block finds its plane from its index (sequences in the order of falling budget, then
+// layers, heads, slabs), the list of a sequence comes by value with the launch (up to
+// COMPACT_INLINE lists) or from a small uploaded table, and the token and position ids are
+// moved by the first blocks of the same launch.  A table upload before the cache's kernel and
+// an ids kernel behind it (4 us for a list of 512, 17 us for 4096) stood in line before.
+#include <algorithm>
+
 #include "cc_internal.h"
 
 namespace cc {
@@ -21,14 +29,77 @@ constexpr int CU = 5;         // 16-byte row pieces in flight per thread per chu
 
 struct CompactArgs {
   KvView src[2], dst[2];
-  int row16;                  // row bytes / 16
+  int row16;                  // 16-byte pieces of a row in one column slab
+  int n_slabs;                // column slabs of a row (planes of their own)
   const int32_t* keep;
-  const CompactList* lists;
-  const CompactPlane* planes;
-  int n_planes;
-  int n_tensors;              // 1 (ids layout of one tensor) or 2 (keys and values)
+  const CompactList* lists_d; // null: lists
+  int n_seqs, n_layers, n_heads, per_head;
+  int n_tensors;              // 1 (rows of one array) or 2 (keys and values)
   int rows_per_chunk;         // (CNT / row16) * CU
+  int id_blocks;              // leading blocks that move the ids, one for each sequence
+  int32_t* ids[2];
+  const int32_t* cu;
+  CompactList lists[COMPACT_INLINE];   // sorted: see CompactList
 };
+
+struct Plane {
+  int seq, layer, head, tensor;
+  int64_t tok0;
+  int k;
+  const int32_t* keep;
+  int col;                    // first byte of the slab
+};
+
+__device__ __forceinline__ CompactList list_of(const CompactArgs& a, int i) {
+  return a.lists_d ? a.lists_d[i] : a.lists[i];
+}
+
+// Block -> plane: keys and values of a plane are adjacent blocks, slabs next, so that a row's
+// pieces are moved at about the same time; the sequences come longest first.
+__device__ __forceinline__ Plane plane_of(const CompactArgs& a, int i) {
+  Plane P;
+  P.tensor = i % a.n_tensors;
+  i /= a.n_tensors;
+  P.col = (i % a.n_slabs) * a.row16 * 16;
+  i /= a.n_slabs;
+  P.head = i % a.n_heads;
+  i /= a.n_heads;
+  P.layer = i % a.n_layers;
+  i /= a.n_layers;
+  const CompactList L = list_of(a, __builtin_amdgcn_readfirstlane(a.per_head ? i * a.n_heads + P.head : i));
+  P.seq = L.seq;
+  P.tok0 = L.tok0;
+  P.k = L.k;
+  P.keep = a.keep + L.keep_off;
+  return P;
+}
+
+// ids[cu_b + j] = ids[cu_b + keep[j]] in place, block i for the i-th sequence's first list.
+__device__ __forceinline__ void compact_ids(const CompactArgs& a, int i) {
+  constexpr int U = 8;
+  const CompactList L = list_of(a, a.per_head ? i * a.n_heads : i);
+  const int32_t* kp = a.keep + L.keep_off;
+  const int base = a.cu[L.seq];
+  for (int j0 = 0; j0 < L.k; j0 += CNT * U) {
+    int32_t x[2][U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int src = base + kp[min(j0 + u * CNT + int(threadIdx.x), L.k - 1)];
+      if (a.ids[0]) x[0][u] = a.ids[0][src];
+      if (a.ids[1]) x[1][u] = a.ids[1][src];
+    }
+    __builtin_amdgcn_s_waitcnt(0);   // loads returned before anyone overwrites a source
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = j0 + u * CNT + threadIdx.x;
+      if (j < L.k) {
+        if (a.ids[0]) a.ids[0][base + j] = x[0][u];
+        if (a.ids[1]) a.ids[1][base + j] = x[1][u];
+      }
+    }
+  }
+}
 
 // A 16-byte piece of a source row, read non-temporally: a kept row is read once and never
 // again, so the load need not stay in the caches.  Measured with the cache flushed, in-place
@@ -54,11 +125,10 @@ struct PagedBufs {
 };
 
 __device__ __forceinline__ void compact_paged_steps(const CompactArgs& a, const KvView& v,
-                                                    const CompactPlane& P, const int32_t* keep,
-                                                    int k, char* base, int sub, int r0,
+                                                    const Plane& P, const int32_t* keep,
+                                                    int k, char* base, int r0,
                                                     int rstep, int esz16, int R, int nch) {
   (void)a;
-  (void)sub;
   const int32_t* bt = v.block_table + int64_t(P.seq) * v.max_pages;
   char* pb = base + int64_t(P.layer) * v.layer_stride + int64_t(P.head) * v.head_stride + esz16;
   auto slot = [&](int c, int u) { return min(c * R + r0 + u * rstep, k - 1); };
@@ -123,21 +193,20 @@ __device__ __forceinline__ void compact_paged_steps(const CompactArgs& a, const 
 
 template <bool PAGED>
 __global__ __launch_bounds__(CNT) void compact_in_place_kernel(CompactArgs a) {
-  // plane-major: the keys and the values of a plane are adjacent workgroups, so the planes
-  // (sorted longest first) start in that order for both tensors when not all are resident
-  const int tensor = blockIdx.x % a.n_tensors;
-  const CompactPlane P = a.planes[blockIdx.x / a.n_tensors];
-  const CompactList L = a.lists[P.list];
-  const int32_t* keep = a.keep + L.keep_off;
-  const int k = L.k;
+  if (int(blockIdx.x) < a.id_blocks) {
+    compact_ids(a, blockIdx.x);
+    return;
+  }
+  const Plane P = plane_of(a, int(blockIdx.x) - a.id_blocks);
+  const int32_t* keep = P.keep;
+  const int k = P.k;
   if (k <= 0) return;
-  const KvView& v = a.src[tensor];   // source and destination views are the same
-  char* base = reinterpret_cast<char*>(const_cast<void*>(v.base)) + L.tok0 * v.tok_stride;
+  const KvView& v = a.src[P.tensor];   // source and destination views are the same
+  char* base = reinterpret_cast<char*>(const_cast<void*>(v.base)) + P.tok0 * v.tok_stride;
   const int tpr = a.row16;
-  const int sub = threadIdx.x % tpr;
   const int r0 = threadIdx.x / tpr;
   const int rstep = CNT / tpr;
-  const int esz16 = sub * 16;
+  const int esz16 = P.col + (threadIdx.x % tpr) * 16;
   const int R = a.rows_per_chunk;
   const int nch = (k + R - 1) / R;
   auto load_idx = [&](int c, int (&idx)[CU]) {
@@ -150,7 +219,7 @@ __global__ __launch_bounds__(CNT) void compact_in_place_kernel(CompactArgs a) {
       buf[u] = ldg16(base + kv_off<PAGED>(v, P.seq, P.layer, P.head, idx[u]) + esz16);
   };
   if constexpr (PAGED) {
-    compact_paged_steps(a, v, P, keep, k, base, sub, r0, rstep, esz16, R, nch);
+    compact_paged_steps(a, v, P, keep, k, base, r0, rstep, esz16, R, nch);
     return;
   } else {
     // Loads complete in issue order.  Each chunk step issues the keep indices of chunk c+2
@@ -192,20 +261,21 @@ __global__ __launch_bounds__(CNT) void compact_in_place_kernel(CompactArgs a) {
 
 template <bool PAGED>
 __global__ __launch_bounds__(CNT) void compact_kernel(CompactArgs a) {
-  const int tensor = blockIdx.x % a.n_tensors;
-  const CompactPlane P = a.planes[blockIdx.x / a.n_tensors];
-  const CompactList L = a.lists[P.list];
-  const int32_t* keep = a.keep + L.keep_off;
-  const int k = L.k;
-  const KvView& sv = a.src[tensor];
-  const KvView& dv = a.dst[tensor];
-  const char* sb = reinterpret_cast<const char*>(sv.base) + L.tok0 * sv.tok_stride;
-  char* db = reinterpret_cast<char*>(const_cast<void*>(dv.base)) + L.tok0 * dv.tok_stride;
+  if (int(blockIdx.x) < a.id_blocks) {
+    if (blockIdx.y == 0) compact_ids(a, blockIdx.x);
+    return;
+  }
+  const Plane P = plane_of(a, int(blockIdx.x) - a.id_blocks);
+  const int32_t* keep = P.keep;
+  const int k = P.k;
+  const KvView& sv = a.src[P.tensor];
+  const KvView& dv = a.dst[P.tensor];
+  const char* sb = reinterpret_cast<const char*>(sv.base) + P.tok0 * sv.tok_stride;
+  char* db = reinterpret_cast<char*>(const_cast<void*>(dv.base)) + P.tok0 * dv.tok_stride;
   const int tpr = a.row16;
-  const int sub = threadIdx.x % tpr;
   const int r0 = threadIdx.x / tpr;
   const int rstep = CNT / tpr;
-  const int esz16 = sub * 16;
+  const int esz16 = P.col + (threadIdx.x % tpr) * 16;
   // element size is folded into the strides: the views carry byte strides here
   const int j_begin = blockIdx.y * a.rows_per_chunk;
   const int j_end = min(k, j_begin + a.rows_per_chunk);
@@ -228,33 +298,6 @@ __global__ __launch_bounds__(CNT) void compact_kernel(CompactArgs a) {
   }
 }
 
-// ids[cu_b + j] = ids[cu_b + keep[j]] in place for one sequence's first list.
-__global__ __launch_bounds__(CNT) void compact_ids_kernel(int32_t* ids0, int32_t* ids1,
-                                                          const int32_t* cu,
-                                                          const int32_t* keep,
-                                                          const CompactList* lists,
-                                                          const int32_t* seq_list) {
-  const int b = blockIdx.x;
-  const CompactList L = lists[seq_list[b]];
-  const int32_t* kp = keep + L.keep_off;
-  const int base = cu[b];
-  for (int j0 = 0; j0 < L.k; j0 += CNT) {
-    const int j = j0 + threadIdx.x;
-    int32_t a0 = 0, a1 = 0;
-    if (j < L.k) {
-      const int src = base + kp[j];
-      if (ids0) a0 = ids0[src];
-      if (ids1) a1 = ids1[src];
-    }
-    __builtin_amdgcn_s_waitcnt(0);   // loads returned before anyone overwrites a source
-    __syncthreads();
-    if (j < L.k) {
-      if (ids0) ids0[base + j] = a0;
-      if (ids1) ids1[base + j] = a1;
-    }
-  }
-}
-
 }  // namespace
 
 hipError_t launch_compact(const CompactLaunch& c, hipStream_t s) {
@@ -262,40 +305,55 @@ hipError_t launch_compact(const CompactLaunch& c, hipStream_t s) {
   for (int t = 0; t < 2; ++t) {
     a.src[t] = c.src[t];
     a.dst[t] = c.dst[t];
+    a.ids[t] = c.ids[t];
   }
-  a.row16 = c.row_bytes / 16;
   a.keep = c.keep;
-  a.lists = c.lists_d;
-  a.planes = c.planes_d;
-  a.n_planes = c.n_planes;
+  a.lists_d = c.lists_d;
+  a.n_seqs = c.n_seqs;
+  a.n_layers = c.n_layers;
+  a.n_heads = c.n_heads;
+  a.per_head = c.per_head;
   a.n_tensors = c.n_tensors;
-  a.rows_per_chunk = (CNT / a.row16) * CU;
-  if (c.n_planes > 0) {
-    if (c.in_place) {
-      dim3 grid(c.n_tensors * c.n_planes);
-      if (c.paged)
-        hipLaunchKernelGGL(compact_in_place_kernel<true>, grid, dim3(CNT), 0, s, a);
-      else
-        hipLaunchKernelGGL(compact_in_place_kernel<false>, grid, dim3(CNT), 0, s, a);
-    } else {
-      // chunks sized by the longest list; planes with shorter lists exit early
-      dim3 grid(c.n_tensors * c.n_planes, (c.max_k + a.rows_per_chunk - 1) / a.rows_per_chunk);
-      if (grid.y > 0) {
-        if (c.paged)
-          hipLaunchKernelGGL(compact_kernel<true>, grid, dim3(CNT), 0, s, a);
-        else
-          hipLaunchKernelGGL(compact_kernel<false>, grid, dim3(CNT), 0, s, a);
-      }
-    }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+  a.cu = c.cu_d;
+  a.id_blocks = (c.ids[0] || c.ids[1]) ? c.n_seqs : 0;
+  if (!c.lists_d) {
+    const int n = c.n_seqs * (c.per_head ? c.n_heads : 1);
+    if (n > COMPACT_INLINE) return hipErrorInvalidValue;
+    std::copy(c.lists_h, c.lists_h + n, a.lists);
   }
-  if ((c.ids[0] || c.ids[1]) && c.n_seqs > 0) {
-    hipLaunchKernelGGL(compact_ids_kernel, dim3(c.n_seqs), dim3(CNT), 0, s, c.ids[0], c.ids[1],
-                       c.cu_d, c.keep, c.lists_d, c.seq_list_d);
-    return hipGetLastError();
+  if (c.n_seqs == 0 || c.max_k == 0) return hipSuccess;
+  const int64_t planes = int64_t(c.n_tensors) * c.n_seqs * c.n_layers * c.n_heads;
+  // In place, a plane is one block walking its list.  Few planes with long lists leave most of
+  // the chip idle and make the walk the launch's length: rows are then cut into column slabs (of
+  // at least 64 bytes: half a cache line) while that leaves at most one block a CU and more than
+  // 16 chunks in line.  Keeping 13200 of 20000 entries in 8 planes of 256-byte rows, selection
+  // included: 136 us whole, 85 us in four slabs; 5000 of 20000 in 32 planes 77 and 59 us; lists of
+  // 1024 in 32 planes are faster whole (38 and 42 us), and 64 planes of 19800 about even.  (Blocks
+  // of 1024 threads measured no better anywhere.)
+  a.n_slabs = 1;
+  a.row16 = c.row_bytes / 16;
+  auto chunk = [&]() { return (CNT / a.row16) * CU; };
+  while (c.in_place && a.row16 > 4 && a.row16 % 2 == 0 && planes * a.n_slabs * 2 <= 256 && c.max_k > 16 * chunk()) {
+    a.row16 /= 2;
+    a.n_slabs *= 2;
   }
-  return hipSuccess;
+  a.rows_per_chunk = chunk();
+  const int64_t blocks = planes * a.n_slabs + a.id_blocks;
+  if (blocks > INT32_MAX) return hipErrorInvalidValue;
+  if (c.in_place) {
+    if (c.paged)
+      hipLaunchKernelGGL(compact_in_place_kernel<true>, dim3(unsigned(blocks)), dim3(CNT), 0, s, a);
+    else
+      hipLaunchKernelGGL(compact_in_place_kernel<false>, dim3(unsigned(blocks)), dim3(CNT), 0, s, a);
+  } else {
+    // chunks sized by the longest list; planes with shorter lists exit early
+    const dim3 grid(unsigned(blocks), (c.max_k + a.rows_per_chunk - 1) / a.rows_per_chunk);
+    if (c.paged)
+      hipLaunchKernelGGL(compact_kernel<true>, grid, dim3(CNT), 0, s, a);
+    else
+      hipLaunchKernelGGL(compact_kernel<false>, grid, dim3(CNT), 0, s, a);
+  }
+  return hipGetLastError();
 }
 
 }  // namespace cc
