@@ -152,8 +152,13 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 def _stream(stream=None):
+    """The handle of `stream`, by default of the current one of the current device.  Taken
+    without building a torch.cuda.Stream: that object costs 5 to 10 us of host time, half of
+    what a call on a short cache takes in all."""
     if stream is None:
-        stream = torch.cuda.current_stream()
+        if not torch.cuda.is_initialized():
+            torch.cuda.init()
+        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
     return ctypes.c_void_p(stream.cuda_stream)
 
 
@@ -180,9 +185,11 @@ def problem(*, dtype: str, cu_seqlens: Sequence[int], n_heads_q: int, n_heads_kv
             head_dim: int, hidden: int, vocab: int, device="cuda", mode: str = "last_layer",
             diag: str = "strict", n_layers: int = 0, ffn: int = 0, softmax_scale: float = 0.0,
             rope_theta: float = 0.0, rms_eps: float = 0.0, n_frozen: int = 0,
-            lmhead_packed: bool = False) -> Problem:
+            lmhead_packed: bool = False, cu_device: Optional[torch.Tensor] = None) -> Problem:
+    """cu_device: the int32 values of cu_seqlens already on the device (the default copies
+    them there and waits for the copy, so the problem may be used on any stream)."""
     cu_h = torch.as_tensor(list(cu_seqlens), dtype=torch.int32).contiguous()
-    cu_d = cu_h.to(device)
+    cu_d = cu_h.to(device) if cu_device is None else cu_device
     s = c_problem()
     s.dtype = {"f32": CC_F32, "bf16": CC_BF16}[dtype]
     s.mode = {"last_layer": CC_MODE_LAST_LAYER, "full": CC_MODE_FULL,
@@ -289,9 +296,8 @@ def cc_score_workspace(p: Problem) -> int:
 
 def cc_score(p: Problem, inp: Inputs, scores: torch.Tensor, workspace: Optional[torch.Tensor] = None,
              stream=None) -> torch.Tensor:
-    need = cc_score_workspace(p)
     if workspace is None:
-        workspace = _workspace(need, p.device)
+        workspace = _workspace(cc_score_workspace(p), p.device)
     _check(_lib.cc_score(ctypes.byref(p.struct), ctypes.byref(inp.struct), _ptr(scores),
                          _ptr(workspace), workspace.numel(), _stream(stream)), "cc_score")
     return scores
@@ -436,9 +442,18 @@ def cc_select_workspace(n_segs: int) -> int:
     return _query(_lib.cc_select_workspace, n_segs)
 
 
-def _host_array(x, dtype):
-    """A C-contiguous numpy array of the given integer type (no copy if it is one)."""
-    return np.ascontiguousarray(np.asarray(x), dtype=dtype)
+def _host_array(x, dtype, ctype):
+    """x as a C array of integers to pass by pointer: a plain list or tuple of ints directly,
+    anything else through a C-contiguous numpy array (no copy if it is one of that type)."""
+    if type(x) in (list, tuple):
+        try:
+            return (ctype * len(x))(*x)
+        except TypeError:
+            pass
+    a = np.ascontiguousarray(np.asarray(x), dtype=dtype)
+    arr = ctypes.cast(a.ctypes.data, ctypes.POINTER(ctype))
+    arr._keep = a
+    return arr
 
 
 def cc_select_keep(scores: torch.Tensor, seg_start: Sequence[int], seg_len: Sequence[int],
@@ -446,17 +461,14 @@ def cc_select_keep(scores: torch.Tensor, seg_start: Sequence[int], seg_len: Sequ
                    workspace: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """seg_start, seg_len, k: host sequences or numpy arrays (int64, int32, int32 arrays
     are passed without a copy)."""
-    st = _host_array(seg_start, np.int64)
-    ln = _host_array(seg_len, np.int32)
-    kk = _host_array(k, np.int32)
-    n = len(ln)
+    st = _host_array(seg_start, np.int64, _i64)
+    ln = _host_array(seg_len, np.int32, _i32)
+    kk = _host_array(k, np.int32, _i32)
+    n = len(seg_len)
     if workspace is None:
         workspace = _workspace(cc_select_workspace(n), scores.device)
-    _check(_lib.cc_select_keep(_ptr(scores), n, st.ctypes.data_as(ctypes.POINTER(_i64)),
-                               ln.ctypes.data_as(ctypes.POINTER(_i32)),
-                               kk.ctypes.data_as(ctypes.POINTER(_i32)), _ptr(keep_idx),
-                               _ptr(workspace), workspace.numel(), _stream(stream)),
-           "cc_select_keep")
+    _check(_lib.cc_select_keep(_ptr(scores), n, st, ln, kk, _ptr(keep_idx), _ptr(workspace),
+                               workspace.numel(), _stream(stream)), "cc_select_keep")
     return keep_idx
 
 

@@ -90,13 +90,20 @@ class RefreshLoop:
         self.n += m
 
     # ---------------------------------------------------------------- refresh cycle
-    def problem(self) -> cc.Problem:
+    def problem(self, cu_device: Optional[torch.Tensor] = None) -> cc.Problem:
         m = self.m
         return cc.problem(dtype="bf16", cu_seqlens=[0, self.n], n_heads_q=m.n_heads_q,
                           n_heads_kv=m.n_heads_kv, head_dim=m.head_dim, hidden=m.hidden,
                           vocab=m.vocab, device=self.device, mode=m.mode, ffn=m.ffn,
                           rope_theta=m.rope_theta, rms_eps=m.rms_eps,
-                          lmhead_packed=m.w_lm_packed is not None)
+                          lmhead_packed=m.w_lm_packed is not None, cu_device=cu_device)
+
+    def _queued_problem(self) -> cc.Problem:
+        """problem(), its device lengths written by the current stream: no wait for a copy
+        (2% of a pass of 768 entries when passes follow each other)."""
+        cu = torch.zeros(2, dtype=torch.int32, device=self.device)
+        cu[1:].fill_(self.n)
+        return self.problem(cu)
 
     def inputs(self) -> cc.Inputs:
         m, n = self.m, self.n
@@ -110,7 +117,7 @@ class RefreshLoop:
     def scores(self) -> torch.Tensor:
         """Counter-causal surprise of every cached entry (the last one is +inf)."""
         s = torch.empty(self.n, dtype=torch.float32, device=self.device)
-        cc.cc_score(self.problem(), self.inputs(), s)
+        cc.cc_score(self._queued_problem(), self.inputs(), s)
         return s
 
     def refresh(self, hook: Optional[Callable] = None) -> torch.Tensor:
@@ -118,7 +125,7 @@ class RefreshLoop:
         they were).  `hook(scores, keep)` sees both before the cache is rewritten."""
         if self.n <= self.J:
             return torch.arange(self.n, dtype=torch.int32, device=self.device)
-        p = self.problem()
+        p = self._queued_problem()
         s = self.scores()
         keep = torch.empty(self.J, dtype=torch.int32, device=self.device)
         cc.cc_select_keep(s, [0], [self.n], [self.J], keep)
