@@ -60,14 +60,14 @@ typedef __attribute__((address_space(1))) const void global_void;
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef short v8i16 __attribute__((ext_vector_type(8)));
 
+template <class Items>
 struct AttnArgs {
   const u16* q;
   u16* o;
-  const int32_t* cu;
-  const int4* work;   // null for one sequence: item i is (0, i % nkv, i / nkv)
+  Items items;
   KvView k, v;
   int layer;
-  int hq, g, nkv;
+  int hq, g;
   float c2;        // scale * log2(e)
   int inclusive;
 };
@@ -129,29 +129,38 @@ __device__ __forceinline__ void page_numbers(const int32_t* p0, const int32_t* p
                : "s"(p0), "s"(p1), "s"(p2), "s"(p3) : "memory");
 }
 
-template <int HD, bool PAGED>
-__global__ __launch_bounds__(256, 2) void attn_cc_bf16(AttnArgs a) {
+// KS key groups of four waves share an item's rows: group kg takes key tiles tb + kg, tb + kg +
+// KS, ... through buffers of its own, and the groups' (max, sum, output) merge through LDS at
+// the end.  KS = 1 is the kernel described above.  KS = 2 halves the serial chain of tiles of an
+// item and is for launches of at most one item a CU, where a workgroup has its CU to itself and
+// each SIMD only one wave, with at least 12 tiles to share: one group against two, 8 heads of 128
+// on one KV head: 1500 entries 29.7 and 26.6 us, 3000 entries 53 and 45; 8 heads of 64, 3000
+// entries 45 and 34.5; 28 heads of 128 on four KV heads: 900 entries 23.3 and 22.1, 512 entries
+// 15.2 and 15.6 (each tile costs a shared CU more, and the merge is a barrier).
+template <int HD, bool PAGED, int KS, class Items>
+__global__ __launch_bounds__(256 * KS, 2) void attn_cc_bf16(AttnArgs<Items> a) {
   using SH = Shape<HD>;
   constexpr int TILE = SH::TILE, ROWB = SH::ROWB, CPR = SH::CPR, RPW = SH::RPW, NI = SH::NI;
   constexpr int NKS = SH::NKS, NDB = SH::NDB, NS = SH::NS, NPV = SH::NPV;
   // Two K and two V buffers as distinct objects: the compiler can then tell the buffer a
   // DMA is filling from the one being read, and waits for the DMA only where asked.
-  __shared__ __attribute__((aligned(1024))) u16 kl0[TILE];
-  __shared__ __attribute__((aligned(1024))) u16 kl1[TILE];
-  __shared__ __attribute__((aligned(1024))) u16 vl0[TILE];
-  __shared__ __attribute__((aligned(1024))) u16 vl1[TILE];
+  __shared__ __attribute__((aligned(1024))) u16 kb0[KS * TILE];
+  __shared__ __attribute__((aligned(1024))) u16 kb1[KS * TILE];
+  __shared__ __attribute__((aligned(1024))) u16 vb0[KS * TILE];
+  __shared__ __attribute__((aligned(1024))) u16 vb1[KS * TILE];
 
-  // work item: from the table, or for one sequence from the block index (row blocks in
-  // increasing order, heaviest first, KV heads fastest: the table's order)
-  const int4 w = a.work ? a.work[blockIdx.x]
-                        : make_int4(0, int(blockIdx.x) % a.nkv, int(blockIdx.x) / a.nkv, 0);
-  const int b = w.x, kvh = w.y, rb = w.z;
-  const int seq0 = a.cu[b];
-  const int n = a.cu[b + 1] - seq0;
+  const AttnItem w = a.items.item(blockIdx.x);
+  const int b = w.seq, kvh = w.kvh, rb = w.rb;
+  const int seq0 = w.seq0, n = w.n;
   const int g = a.g;
   const int nrows = n * g;
   const int tid = threadIdx.x;
-  const int wave = tid >> 6, lane = tid & 63;
+  const int wave = (tid >> 6) & (NWAVES - 1), lane = tid & 63;
+  const int kg = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 8);
+  u16* const kl0 = kb0 + kg * TILE;
+  u16* const kl1 = kb1 + kg * TILE;
+  u16* const vl0 = vb0 + kg * TILE;
+  u16* const vl1 = vb1 + kg * TILE;
   const int hi = lane >> 5, col = lane & 31;
 
   const int row = rb * ROWS + wave * ROWS_W + col;
@@ -176,11 +185,11 @@ __global__ __launch_bounds__(256, 2) void attn_cc_bf16(AttnArgs a) {
   const int wg_last = min(row0 + ROWS, nrows) - 1;
   const int pos_hi_wg = row0 + ROWS > nrows ? n : wg_last / g;   // partial blocks mask always
   const int first_key = pos_lo + (a.inclusive ? 0 : 1);
-  const int tb = first_key / BN;
+  const int tb0 = first_key / BN;
   const int te = (n + BN - 1) / BN;
-  if (tb >= te) {
+  if (tb0 >= te) {
     // no key reachable from any row of the block: every output row is 0
-    if (valid) {
+    if (valid && kg == 0) {
       u16* op = a.o + (int64_t(seq0 + pos) * a.hq + hq) * HD + hi * 4;
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
@@ -190,8 +199,9 @@ __global__ __launch_bounds__(256, 2) void attn_cc_bf16(AttnArgs a) {
     }
     return;
   }
-  // tiles [tb, tm0) and [tm1, te) need the mask; [tm0, tm1) see every key of every row
-  const int tm0 = min(te, max(tb, (pos_hi_wg + 1 + BN - 1) / BN));
+  const int tb = tb0 + kg;   // this group's first tile (the last group may have none)
+  // tiles [tb0, tm0) and [tm1, te) need the mask; [tm0, tm1) see every key of every row
+  const int tm0 = min(te, max(tb0, (pos_hi_wg + 1 + BN - 1) / BN));
   const int tm1 = (n % BN == 0) ? te : te - 1;
 
   // ---- tile DMA (global -> LDS, no registers).  Wave w, instruction i fills the RPW tile
@@ -338,21 +348,23 @@ __global__ __launch_bounds__(256, 2) void attn_cc_bf16(AttnArgs a) {
 #pragma unroll
   for (int db = 0; db < NDB; ++db) acc[db] = f32x16{};
 
-  // contiguous caches: tile pointers of the next K (t + 2) and V (t + 1) DMAs, in bytes
+  // contiguous caches: tile pointers of the next K (t + 2 KS) and V (t + KS) DMAs, in bytes
   const int64_t kstep = int64_t(BN) * kts, vstep = int64_t(BN) * vts;
-  const char* kptr = kplane + int64_t(tb + 2) * kstep;
-  const char* vptr = vplane + int64_t(tb + 1) * vstep;
+  const char* kptr = kplane + int64_t(tb + 2 * KS) * kstep;
+  const char* vptr = vplane + int64_t(tb + KS) * vstep;
   // Paged caches: the page numbers of the tiles the next step loads are fetched at the end
   // of the step before (a tile's K pages are the next step's V pages), so no step waits for
-  // a scalar load before its DMAs.  kpg: pages of tile t + 2 (K), vpg: of tile t + 1 (V).
+  // a scalar load before its DMAs.  kpg: pages of the group's tile after next (K), vpg: of its next tile (V).
   int kpg[NI], vpg[NI];
   // prologue: K(tb), V(tb), K(tb+1) in LDS; S(tb) and its unmasked row max in registers.
+  if (KS == 1 || tb < te) {
   load_pages(tb, kpg);
   issue(kl0, tb, a.k, kplane, kplane + int64_t(tb) * kstep, klane, kch, kts, kpg);
   issue(vl0, tb, a.v, vplane, vplane + int64_t(tb) * vstep, vlane, vch, vts, kpg);
-  load_pages(tb + 1, vpg);
-  if (tb + 1 < te) issue(kl1, tb + 1, a.k, kplane, kplane + int64_t(tb + 1) * kstep, klane, kch, kts, vpg);
-  if (tb + 2 < te) load_pages(tb + 2, kpg);
+  load_pages(tb + KS, vpg);
+  if (tb + KS < te) issue(kl1, tb + KS, a.k, kplane, kplane + int64_t(tb + KS) * kstep, klane, kch, kts, vpg);
+  if (tb + 2 * KS < te) load_pages(tb + 2 * KS, kpg);
+  }
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   f32x16 sa[2], sb[2];
@@ -376,10 +388,10 @@ __global__ __launch_bounds__(256, 2) void attn_cc_bf16(AttnArgs a) {
     const u16* Vc = P ? vl1 : vl0;
     u16* Vfree = P ? vl0 : vl1;
     // tiles past the last are never read: nothing to load
-    if (t + 2 < te) issue(Kfree, t + 2, a.k, kplane, kptr, klane, kch, kts, kpg);
-    if (t + 1 < te) issue(Vfree, t + 1, a.v, vplane, vptr, vlane, vch, vts, vpg);
-    kptr += kstep;
-    vptr += vstep;
+    if (t + 2 * KS < te) issue(Kfree, t + 2 * KS, a.k, kplane, kptr, klane, kch, kts, kpg);
+    if (t + KS < te) issue(Vfree, t + KS, a.v, vplane, vptr, vlane, vch, vts, vpg);
+    kptr += KS * kstep;
+    vptr += KS * vstep;
     bf16x8 kf[4];
     kf[0] = kfrag(Kn, 0);
     kf[1] = kfrag(Kn, 1);
@@ -486,19 +498,60 @@ __global__ __launch_bounds__(256, 2) void attn_cc_bf16(AttnArgs a) {
       // overlaps the DMA wait below
 #pragma unroll
       for (int i = 0; i < NI; ++i) vpg[i] = kpg[i];
-      if (t + 3 < te) load_pages(t + 3, kpg);
+      if (t + 3 * KS < te) load_pages(t + 3 * KS, kpg);
     }
+  };
+  auto sync = [&]() {
     __builtin_amdgcn_s_waitcnt(0);   // this wave's DMAs have landed
     __syncthreads();                 // everyone's, and everyone is done with K(t+1), V(t)
   };
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
-  for (int t = tb; t < te; t += 2) {
-    step(t, I0{}, t < tm0 || t >= tm1);
-    if (t + 1 < te) step(t + 1, I1{}, t + 1 < tm0 || t + 1 >= tm1);
+  // every group runs the barriers of the first one's tiles
+  for (int t = tb; t - kg < te; t += 2 * KS) {
+    if (KS == 1 || t < te) step(t, I0{}, t < tm0 || t >= tm1);
+    sync();
+    const int u = t + KS;
+    if (u - kg < te) {
+      if (KS == 1 || u < te) step(u, I1{}, u < tm0 || u >= tm1);
+      sync();
+    }
   }
 
-  const float l_tot = l_run + __shfl_xor(l_run, 32);
+  float l_all = l_run + __shfl_xor(l_run, 32);
+  // the wave's output staging: its 32 rows in the K buffers
+  char* stg = reinterpret_cast<char*>(wave < 2 ? kb0 : kb1) + (wave & 1) * (KS * ROWS_W * ROWB);
+  if constexpr (KS == 2) {
+    // group 1 leaves its output in the staging of the same wave of group 0 (32 rows of HD
+    // floats, 16 bytes a lane at a time) and its row maxima and sums in the V buffers
+    float* ml = reinterpret_cast<float*>(vb0) + wave * 128;
+    if (kg == 1) {
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj)
+          *reinterpret_cast<float4*>(stg + ((db * 4 + jj) * 64 + lane) * 16) =
+              make_float4(acc[db][jj * 4], acc[db][jj * 4 + 1], acc[db][jj * 4 + 2], acc[db][jj * 4 + 3]);
+      ml[lane] = m_run;
+      ml[64 + lane] = l_all;
+    }
+    __syncthreads();
+    if (kg == 1) return;
+    const float m1 = ml[lane], M = fmaxf(m_run, m1), ref = M == -INFINITY ? 0.f : M;
+    const float w0 = fast_exp2((m_run - ref) * a.c2), w1 = fast_exp2((m1 - ref) * a.c2);
+    l_all = l_all * w0 + ml[64 + lane] * w1;
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) {
+        const float4 x = *reinterpret_cast<const float4*>(stg + ((db * 4 + jj) * 64 + lane) * 16);
+        acc[db][jj * 4] = acc[db][jj * 4] * w0 + x.x * w1;
+        acc[db][jj * 4 + 1] = acc[db][jj * 4 + 1] * w0 + x.y * w1;
+        acc[db][jj * 4 + 2] = acc[db][jj * 4 + 2] * w0 + x.z * w1;
+        acc[db][jj * 4 + 3] = acc[db][jj * 4 + 3] * w0 + x.w * w1;
+      }
+  }
+  const float l_tot = l_all;
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
   // The output goes out through LDS as whole rows.  The K buffers are free here (the last
   // step waited for every load and ended with a barrier); each wave stages its 32 rows x HD
@@ -508,7 +561,6 @@ __global__ __launch_bounds__(256, 2) void attn_cc_bf16(AttnArgs a) {
   // (head-major), so a wave instruction stores 1 KB of whole rows instead of 64 scattered
   // 8-byte pieces.  LDS operations of one wave complete in order, so the wave needs no
   // barrier of its own.
-  char* stg = reinterpret_cast<char*>(wave < 2 ? kl0 : kl1) + (wave & 1) * (ROWS_W * ROWB);
 #pragma unroll
   for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -531,16 +583,32 @@ __global__ __launch_bounds__(256, 2) void attn_cc_bf16(AttnArgs a) {
   }
 }
 
-void fill_common(AttnArgs& x, const AttnLaunch& a) {
-  x.cu = a.cu_d;
-  x.work = a.work_d;
+template <int KS, class Items>
+hipError_t launch_bf16(const AttnLaunch& a, const Items& items, hipStream_t s) {
+  AttnArgs<Items> x;
+  x.q = static_cast<const u16*>(a.q);
+  x.o = static_cast<u16*>(a.o);
+  x.items = items;
   x.k = a.k;
   x.v = a.v;
   x.layer = a.layer;
   x.hq = a.n_heads_q;
   x.g = a.n_heads_q / a.n_heads_kv;
-  x.nkv = a.n_heads_kv;
+  x.c2 = a.scale * kLog2e;
   x.inclusive = a.inclusive;
+  const dim3 grid(a.n_work), block(256 * KS);
+  if (a.head_dim == 64) {
+    if (a.paged)
+      hipLaunchKernelGGL((attn_cc_bf16<64, true, KS, Items>), grid, block, 0, s, x);
+    else
+      hipLaunchKernelGGL((attn_cc_bf16<64, false, KS, Items>), grid, block, 0, s, x);
+  } else {
+    if (a.paged)
+      hipLaunchKernelGGL((attn_cc_bf16<128, true, KS, Items>), grid, block, 0, s, x);
+    else
+      hipLaunchKernelGGL((attn_cc_bf16<128, false, KS, Items>), grid, block, 0, s, x);
+  }
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -552,26 +620,16 @@ int attention_rows_per_item(int dtype, int head_dim) {
 
 hipError_t launch_attention(const AttnLaunch& a, hipStream_t s) {
   if (a.n_work == 0) return hipSuccess;
-  if (a.dtype == CC_BF16) {
-    AttnArgs x;
-    fill_common(x, a);
-    x.q = static_cast<const u16*>(a.q);
-    x.o = static_cast<u16*>(a.o);
-    x.c2 = a.scale * kLog2e;
-    if (a.head_dim == 64) {
-      if (a.paged)
-        hipLaunchKernelGGL((attn_cc_bf16<64, true>), dim3(a.n_work), dim3(256), 0, s, x);
-      else
-        hipLaunchKernelGGL((attn_cc_bf16<64, false>), dim3(a.n_work), dim3(256), 0, s, x);
-    } else {
-      if (a.paged)
-        hipLaunchKernelGGL((attn_cc_bf16<128, true>), dim3(a.n_work), dim3(256), 0, s, x);
-      else
-        hipLaunchKernelGGL((attn_cc_bf16<128, false>), dim3(a.n_work), dim3(256), 0, s, x);
-    }
-    return hipGetLastError();
+  if (a.dtype != CC_BF16) return launch_attention_f32(a, s);
+  // a table stands for more than ATTN_INLINE sequences: many items
+  if (a.items.table) return launch_bf16<1>(a, a.items, s);
+  // two key groups: at most one item a CU and tiles to share (figures at the kernel)
+  const bool split = a.n_work <= 256 && a.items.seqs[0].n >= 12 * BN;
+  if (a.items.n_seqs == 1) {
+    const AttnOne one{a.items.nkv, a.items.seqs[0].n};
+    return split ? launch_bf16<2>(a, one, s) : launch_bf16<1>(a, one, s);
   }
-  return launch_attention_f32(a, s);
+  return split ? launch_bf16<2>(a, a.items, s) : launch_bf16<1>(a, a.items, s);
 }
 
 }  // namespace cc

@@ -25,14 +25,14 @@ constexpr int F_ROWS = 32;   // rows per workgroup
 constexpr int F_BN = 16;     // keys per tile
 constexpr int F_WAVES = 4;
 
+template <class Items>
 struct AttnArgsF {
   const float* q;
   float* o;
-  const int32_t* cu;
-  const int4* work;   // null for one sequence: item i is (0, i % nkv, i / nkv)
+  Items items;
   KvView k, v;
   int layer;
-  int hq, g, nkv;
+  int hq, g;
   float scale;
   int inclusive;
 };
@@ -47,19 +47,16 @@ __device__ __forceinline__ bool non_finite(float x) {
   return (__float_as_uint(x) & 0x7f800000u) == 0x7f800000u;
 }
 
-template <int D, bool PAGED>
-__global__ __launch_bounds__(64 * F_WAVES) void attn_cc_f32(AttnArgsF a) {
+template <int D, bool PAGED, class Items>
+__global__ __launch_bounds__(64 * F_WAVES) void attn_cc_f32(AttnArgsF<Items> a) {
   constexpr int DL = D / 4;     // dims a lane holds of a key (or query) row
   constexpr int DB = D / 16;    // output blocks; dims a lane holds of a value row
   constexpr int OLD = D + 4;    // padded row of the merge buffer
   __shared__ __attribute__((aligned(16))) float os[F_WAVES][F_ROWS][OLD];
   __shared__ float ms[F_WAVES][F_ROWS], ls[F_WAVES][F_ROWS];
-  // work item: from the table, or for one sequence from the block index (row blocks in
-  // increasing order, heaviest first, KV heads fastest: the table's order)
-  const int4 w = a.work ? a.work[blockIdx.x]
-                        : make_int4(0, int(blockIdx.x) % a.nkv, int(blockIdx.x) / a.nkv, 0);
-  const int b = w.x, kvh = w.y, row0 = w.z * F_ROWS;
-  const int seq0 = a.cu[b], n = a.cu[b + 1] - seq0;
+  const AttnItem w = a.items.item(blockIdx.x);
+  const int b = w.seq, kvh = w.kvh, row0 = w.rb * F_ROWS;
+  const int seq0 = w.seq0, n = w.n;
   const int g = a.g, nrows = n * g;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int grp = lane >> 4, r16 = lane & 15;
@@ -224,37 +221,42 @@ __global__ __launch_bounds__(64 * F_WAVES) void attn_cc_f32(AttnArgsF a) {
   }
 }
 
-}  // namespace
-
-int attention_f32_rows() { return F_ROWS; }
-
-hipError_t launch_attention_f32(const AttnLaunch& a, hipStream_t s) {
-  AttnArgsF x;
+template <class Items>
+hipError_t launch_f32(const AttnLaunch& a, const Items& items, hipStream_t s) {
+  AttnArgsF<Items> x;
+  x.items = items;
   x.q = static_cast<const float*>(a.q);
   x.o = static_cast<float*>(a.o);
-  x.cu = a.cu_d;
-  x.work = a.work_d;
   x.k = a.k;
   x.v = a.v;
   x.layer = a.layer;
   x.hq = a.n_heads_q;
   x.g = a.n_heads_q / a.n_heads_kv;
-  x.nkv = a.n_heads_kv;
   x.scale = a.scale;
   x.inclusive = a.inclusive;
   const dim3 grid(a.n_work), block(64 * F_WAVES);
   if (a.head_dim == 64) {
     if (a.paged)
-      hipLaunchKernelGGL((attn_cc_f32<64, true>), grid, block, 0, s, x);
+      hipLaunchKernelGGL((attn_cc_f32<64, true, Items>), grid, block, 0, s, x);
     else
-      hipLaunchKernelGGL((attn_cc_f32<64, false>), grid, block, 0, s, x);
+      hipLaunchKernelGGL((attn_cc_f32<64, false, Items>), grid, block, 0, s, x);
   } else {
     if (a.paged)
-      hipLaunchKernelGGL((attn_cc_f32<128, true>), grid, block, 0, s, x);
+      hipLaunchKernelGGL((attn_cc_f32<128, true, Items>), grid, block, 0, s, x);
     else
-      hipLaunchKernelGGL((attn_cc_f32<128, false>), grid, block, 0, s, x);
+      hipLaunchKernelGGL((attn_cc_f32<128, false, Items>), grid, block, 0, s, x);
   }
   return hipGetLastError();
+}
+
+}  // namespace
+
+int attention_f32_rows() { return F_ROWS; }
+
+hipError_t launch_attention_f32(const AttnLaunch& a, hipStream_t s) {
+  if (!a.items.table && a.items.n_seqs == 1)
+    return launch_f32(a, AttnOne{a.items.nkv, a.items.seqs[0].n}, s);
+  return launch_f32(a, a.items, s);
 }
 
 }  // namespace cc

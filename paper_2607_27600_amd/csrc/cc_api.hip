@@ -239,19 +239,35 @@ char* at(void* ws, size_t off) { return static_cast<char*>(ws) + off; }
 // call of the same cc_score already did (upload = false).
 cc_status run_attention(const cc_problem* p, const void* q, const cc_kv* kv, int layer, void* o,
                         void* ws, hipStream_t s, bool upload = true) {
-  std::vector<int4> work = attention_work(p);
-  if (work.empty()) return CC_OK;
-  // one sequence: the kernel derives each item from its block index, nothing is uploaded
-  const bool table = p->n_seqs > 1;
-  if (upload && table)
-    CC_HIP(hipMemcpyAsync(ws, work.data(), work.size() * sizeof(int4), hipMemcpyHostToDevice, s));
   AttnLaunch a;
+  a.items.table = nullptr;
+  a.items.cu = p->cu_seqlens_d;
+  a.items.nkv = p->n_heads_kv;
+  a.items.n_seqs = 0;
+  if (p->n_seqs <= ATTN_INLINE) {
+    const int rows_item = attention_rows_per_item(p->dtype, p->head_dim);
+    const int g = p->n_heads_q / p->n_heads_kv;
+    int64_t blocks = 0;
+    for (int b = 0; b < p->n_seqs; ++b) {
+      const int seq0 = p->cu_seqlens_h[b], n = p->cu_seqlens_h[b + 1] - seq0;
+      const int nb = int((int64_t(n) * g + rows_item - 1) / rows_item);
+      a.items.seqs[a.items.n_seqs++] = AttnSeq{b, seq0, n, nb};
+      blocks += nb;
+    }
+    std::stable_sort(a.items.seqs, a.items.seqs + a.items.n_seqs,
+                     [](const AttnSeq& x, const AttnSeq& y) { return x.blocks > y.blocks; });
+    a.n_work = int(blocks * p->n_heads_kv);
+  } else {
+    const std::vector<int4> work = attention_work(p);
+    if (upload && !work.empty())
+      CC_HIP(hipMemcpyAsync(ws, work.data(), work.size() * sizeof(int4), hipMemcpyHostToDevice, s));
+    a.items.table = static_cast<const int4*>(ws);
+    a.n_work = int(work.size());
+  }
+  if (a.n_work == 0) return CC_OK;
   a.dtype = p->dtype;
   a.q = q;
   a.o = o;
-  a.cu_d = p->cu_seqlens_d;
-  a.work_d = table ? static_cast<const int4*>(ws) : nullptr;
-  a.n_work = int(work.size());
   a.k = make_view(kv, kv->k, 1);
   a.v = make_view(kv, kv->v, 1);
   a.paged = kv->layout == CC_KV_PAGED;

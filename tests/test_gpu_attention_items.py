@@ -1,0 +1,33 @@
+"""Attention where its launch changes: work items found from up to 16 sequences by value and from
+the uploaded table beyond, and two key groups a workgroup for launches of at most 256 items (one
+tile, an odd and an even number of tiles, sequences with no key at all)."""
+import numpy as np
+import pytest
+
+from synth import configs as C
+from tests.test_gpu_attention import _check, _run
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("lens,hq,hkv,d,paged", [
+    ((1, 64, 65, 129, 192, 193, 260), 4, 2, 128, False),
+    ((1, 64, 65, 129, 192, 193, 260), 7, 1, 64, True),
+    (tuple(range(3, 99, 6)), 2, 2, 128, True),             # 16 sequences, by value
+    (tuple(range(99, 3, -6)) + (40,), 2, 2, 128, True),    # 17: the table
+    ((700, 100, 701, 0, 1), 32, 8, 128, False),            # more than 256 items
+    ((513,), 28, 4, 128, False),
+])
+@pytest.mark.parametrize("diag", ["strict", "inclusive"])
+def test_bf16(lens, hq, hkv, d, paged, diag):
+    cfg = C.shrink(C.C2, seq_lens=lens, n_heads_q=hq, n_heads_kv=hkv, head_dim=d, paged=paged, cache_layers=1,
+                   keep=(0,) * len(lens))
+    got, ref, _ = _run(cfg, diag)
+    _check(got, ref, "bf16", f"{lens[:4]} {hq}/{hkv} d={d}")
+
+
+def test_f32_many_sequences():
+    for lens in (tuple(range(1, 33, 2)), tuple(range(1, 35, 2))):
+        cfg = C.shrink(C.C1, seq_lens=lens, keep=(0,) * len(lens))
+        got, ref, _ = _run(cfg)
+        _check(got, ref, "f32")
