@@ -443,9 +443,11 @@ def cc_select_workspace(n_segs: int) -> int:
 
 
 def _host_array(x, dtype, ctype):
-    """x as a C array of integers to pass by pointer: a plain list or tuple of ints directly,
-    anything else through a C-contiguous numpy array (no copy if it is one of that type)."""
-    if type(x) in (list, tuple):
+    """x as a C array of integers to pass by pointer: a plain short list or tuple of ints directly,
+    anything else through a C-contiguous numpy array (no copy if it is one of that type).  Up to
+    64 ints are quicker as a C array (8: 1 us against 3 to 5), from 128 on through numpy (1024:
+    67 us against 38)."""
+    if type(x) in (list, tuple) and len(x) <= 64:
         try:
             return (ctype * len(x))(*x)
         except TypeError:
