@@ -1,23 +1,23 @@
 // Keep selection of the memory-refresh cycle (Sec. 3.2): per segment, the k entries that
 // come first under (score descending, ties to the lower index), emitted in ascending
-// index order so the compacted cache keeps the original time order.
+// index order so the compacted cache keeps the original time order.  The order of the scores
+// is that of order_key: -0 == +0, NaN below -inf.
 //
-// One workgroup per segment at a time.  Scores map to order-preserving 32-bit keys (-0 ==
-// +0, NaN below -inf).  8-bit radix passes over the keys (LDS histograms, wave-parallel bucket
-// search) find the k-th largest key T and how many entries equal to T are kept; a final
-// pass in index order emits every key > T and the lowest-index ties with block-wide
-// ballot/prefix counts.  Integer work only: the result is exact.  Launches whose longest
-// segment holds 8193..32768 scores keep every segment in registers (one read of the
-// scores); the others re-read the scores from memory at every pass.
+// One workgroup per segment at a time.  A histogram whose bins cut the range of the segment's
+// finite scores into equal parts finds the bin of the k-th largest score; the few scores of that
+// bin are ranked among each other, which gives the threshold T and how many entries equal to T
+// are kept; a last pass in index order emits every score above T and the lowest-index ties with
+// batched prefix counts.  Rounding moves scores between bins, but never against their order, and
+// everything behind the histogram compares exactly: the result is exact.
+//
+// Segments of up to 32768 scores are read once, into registers, by one of four sizes of the
+// kernel; longer ones are read again by each of the four passes.
 #include <algorithm>
 
 #include "cc_internal.h"
 
 namespace cc {
 namespace {
-
-constexpr int SNT = 1024;           // threads per segment
-constexpr int SWAVES = SNT / 64;
 
 // Descriptor of segment b: computed for regular launches, else by value in the kernel
 // arguments (the first SEL_INLINE) or from the uploaded table.
@@ -62,159 +62,40 @@ __device__ __forceinline__ uint32_t order_key(float f) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// Exclusive prefix count of `flag` over the workgroup (in thread order) and the total.
-__device__ __forceinline__ int block_scan(bool flag, int* wsum, int& total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint64_t bal = __ballot(flag);
-  const int below = __popcll(bal & ((1ull << lane) - 1ull));
-  if (lane == 0) wsum[wave] = __popcll(bal);
-  __syncthreads();
-  int before = 0, tot = 0;
-#pragma unroll
-  for (int w = 0; w < SWAVES; ++w) {
-    const int c = wsum[w];
-    before += w < wave ? c : 0;
-    tot += c;
-  }
-  __syncthreads();
-  total = tot;
-  return before + below;
-}
-
-__global__ __launch_bounds__(SNT) void select_keep_kernel(const float* __restrict__ scores,
-                                                          const SelSeg* __restrict__ segs,
-                                                          SelInline inl,
-                                                          int32_t* __restrict__ keep) {
-  __shared__ uint32_t hist[256];
-  __shared__ int wsum[SWAVES];
-  __shared__ uint32_t sh_digit, sh_rem, sh_cnt;
-  const SelSeg sg = seg_desc(inl, segs, int(blockIdx.x));
-  const float* s = scores + sg.start;
-  int32_t* out = keep + sg.out;
-  const int n = sg.len, k = sg.k;
-  const int tid = threadIdx.x;
-  if (k <= 0) return;
-  if (k >= n) {
-    for (int i = tid; i < n; i += SNT) out[i] = i;
-    return;
-  }
-
-  uint32_t prefix = 0u, mask = 0u, rem = uint32_t(k);
-  for (int pass = 0; pass < 4; ++pass) {
-    const int shift = 24 - 8 * pass;
-    for (int i = tid; i < 256; i += SNT) hist[i] = 0u;
-    __syncthreads();
-    for (int i = tid; i < n; i += SNT) {
-      const uint32_t key = order_key(s[i]);
-      if ((key & mask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1u);
-    }
-    __syncthreads();
-    if (tid < 64) {
-      // lane l owns digits 255-4l .. 252-4l (descending); find the bucket holding the
-      // rem-th largest candidate.
-      const int lane = tid;
-      uint32_t c[4], sum = 0u;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        c[j] = hist[255 - 4 * lane - j];
-        sum += c[j];
-      }
-      const uint32_t incl = wave_incl_scan(sum, lane);   // over lanes (descending digits)
-      const uint32_t excl = incl - sum;
-      if (excl < rem && incl >= rem) {
-        uint32_t acc = excl;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          if (acc + c[j] >= rem) {
-            sh_digit = uint32_t(255 - 4 * lane - j);
-            sh_rem = rem - acc;
-            sh_cnt = c[j];
-            break;
-          }
-          acc += c[j];
-        }
-      }
-    }
-    __syncthreads();
-    prefix |= sh_digit << shift;
-    mask |= 255u << shift;
-    rem = sh_rem;
-    __syncthreads();
-  }
-  const uint32_t T = prefix;   // the k-th largest key; keep `rem` of the entries equal to T
-  // the last pass's bucket holds exactly the keys equal to T: when all of them are kept,
-  // ties need no ranking
-  const bool all_ties = sh_cnt == rem;
-
-  int ties_before = 0, emitted = 0;
-  for (int base = 0; base < n; base += SNT) {
-    const int i = base + tid;
-    const uint32_t key = i < n ? order_key(s[i]) : 0u;
-    const bool eq = i < n && key == T;
-    const bool gt = i < n && key > T;
-    int eq_total = 0, tie_rank = 0;
-    if (!all_ties) tie_rank = ties_before + block_scan(eq, wsum, eq_total);
-    const bool take = gt || (eq && (all_ties || uint32_t(tie_rank) < rem));
-    int take_total;
-    const int pos = emitted + block_scan(take, wsum, take_total);
-    if (take) out[pos] = i;
-    ties_before += eq_total;
-    emitted += take_total;
-  }
-}
-
-// ------------------------------------------------------------------ register path
-// Segments of up to RMAX scores: the workgroup reads its segment once into registers and
-// never touches it again.  The segment is cut into 8 chunks of 4096 scores; thread t of
-// 1024 holds scores 4t .. 4t+3 of every chunk (one 16-byte load per chunk, 1 KB per wave
-// instruction), so index order is (chunk, thread, slot).  The kernel is bound by vector ALU
-// issue, so every per-key step is kept to a few instructions:
-//  - Keys: the float's sign and magnitude turned into a signed two's complement integer
-//    (-0 and +0 both become 0).  NaN keys then lie outside the keys of -inf .. +inf; a
-//    segment that holds any (seen in its extremes) sets them all to one key below -inf.
-//  - Extremes: the smallest key kmin and the largest key other than +inf (a max over
-//    key + 2^23, where +inf alone wraps to the bottom).  The radix digits run on
-//    rel = min(key - kmin, rcap), rcap = that largest key - kmin + 1: +inf keys become rcap,
-//    one above every finite key, and the first digit spreads over the finite scores'
-//    actual range (the +inf of a sequence's last entry would otherwise squeeze them all
-//    into one bucket).
-//  - One 11-bit pass over every key (no test: the first digit holds the top bits of every
-//    rel) into a 2048-bin LDS histogram.  An 11-bit digit leaves about an eighth of the keys
-//    an 8-bit one would in the bucket that holds the threshold, and spreads a wave's atomics
-//    over more bins, so fewer lanes of one instruction collide.  When that bucket has at
-//    most CMAX keys, they copy their low bits to LDS (positions from one LDS counter) and
-//    one wave finishes the lower digits on that list (9 bits a pass, no block-wide
-//    barrier); otherwise further 11-bit block-wide passes run over the registers.
+// ------------------------------------------------------------------ the kernel
+// NT threads hold a tile of CH chunks of 4 NT scores: thread t holds scores 4t .. 4t+3 of every
+// chunk (one 16-byte load per chunk, 1 KB per wave instruction), so index order is (chunk,
+// thread, slot).  STREAM: a segment may span several tiles, and each pass reads them all again;
+// otherwise the one tile stays in registers.  Bound by vector ALU issue and LDS atomics:
+//  - Extremes of the finite scores, so that an infinite one (that of a sequence's last entry)
+//    does not squeeze all others into one bin.
+//  - bin = (f - fmin) * (NB - 2) / (fmax - fmin), clamped to 0 .. NB - 1: subtraction, product,
+//    clamp and truncation are monotone, so a higher bin never holds a lower score, whatever the
+//    rounding (a range that overflows or vanishes leaves one or two bins).  Digits of the float's
+//    bits in its place put scores between 8 and 16 nats, where most lie, into 8 bins: lanes of one
+//    instruction collide on them, and the threshold's bin holds thousands of scores.
+//    Selection calls back to back, float digits -> these bins: 4096 of 32768 scores in each of
+//    eight segments 25.7 -> 15.4 us, 514 of 768 scores 15.2 -> 8.3 us (four 8-bit digits before),
+//    16384 of 131072 scores 246 -> 51 us (likewise, 4-byte loads before).
+//  - NaN scores enter no bin: when the bins hold fewer than k scores, T is NaN.
+//  - Up to CMAX scores of T's bin go to an LDS list (in any order).  Up to RANK of them are ranked
+//    by comparing each with all; more are searched by block-wide digits of their offset from the
+//    bin's smallest, and beyond CMAX that search runs over the tiles in place of the list.
 //  - Bucket searches are two-level wave scans: lane sums over the lanes' bin ranges, then
 //    the bins of the lane that holds the rank.
-//  - Emission: a thread's flagged keys per chunk are counted, and one batched scan over
-//    the workgroup (8 chunk counts per thread, two per word) gives every flagged key its
-//    rank in index order: first for the ties (when not all of them are kept), then for
-//    the kept keys, which each thread stores at their ranks (consecutive keys of a chunk
-//    at consecutive ranks) through a buffer descriptor bounded by the segment's budget.
+//  - Emission: a thread's flagged scores per chunk are counted, and one batched scan over
+//    the workgroup (two chunk counts per word) gives every flagged score its rank in index
+//    order: first for the ties (when not all of them are kept), then for the kept scores, which
+//    each thread stores at their ranks through a buffer descriptor bounded by the segment's
+//    budget.
 constexpr int RNT = 1024;
-constexpr int RWAVES = RNT / 64;
 constexpr int RCW = 4;                 // scores per thread per chunk
-constexpr int RCH = 8;                 // chunks
-constexpr int RCHUNK = RNT * RCW;      // scores per chunk
-constexpr int RPT = RCH * RCW;         // scores per thread
-constexpr int RMAX = RNT * RPT;
-constexpr int CMAX = 4096;             // candidate list of the one-wave finish
-constexpr int SD = 11;                 // bits of a block-wide digit
-constexpr int SBINS = 1 << SD;
-constexpr int WD = 9;                  // bits of a digit of the one-wave finish
-constexpr int WBINS = 1 << WD;
-constexpr int32_t KEY_PINF = 0x7f800000;    // key of +inf
-constexpr int32_t KEY_NINF = -0x7f800000;   // key of -inf
-constexpr int32_t KEY_NAN = KEY_NINF - 1;   // key of every NaN
-constexpr uint32_t FIN_SHIFT = 0x00800000u; // key + FIN_SHIFT wraps +inf, and only +inf, to INT_MIN
-constexpr int32_t I32_MAX = 0x7fffffff;
-constexpr int32_t I32_MIN = -I32_MAX - 1;
+constexpr int CMAX = 4096;             // candidate list
+constexpr uint32_t RANK = 256;         // candidates ranked by comparison
 
-// Signed order key of a float's bits: sign and magnitude to two's complement.
-__device__ __forceinline__ int32_t skey(uint32_t u) {
-  const uint32_t t = uint32_t(int32_t(u) >> 31);
-  return int32_t((u ^ t) + (t & 0x80000001u));
+// The float of an order key.
+__device__ __forceinline__ float key_float(uint32_t k) {
+  return __uint_as_float((k & 0x80000000u) ? k ^ 0x80000000u : ~k);
 }
 
 // Inclusive scan inside each row of 16 lanes (row 0 holds lanes 0..15).
@@ -234,37 +115,40 @@ __device__ __forceinline__ uint32_t row0_reduce(uint32_t x, uint32_t identity, O
   x = op(x, dpp_move<0x118, 0xf>(x, identity));
   return uint32_t(__builtin_amdgcn_readlane(int(x), 15));
 }
-constexpr auto imin = [](uint32_t a, uint32_t b) { return uint32_t(min(int32_t(a), int32_t(b))); };
-constexpr auto imax = [](uint32_t a, uint32_t b) { return uint32_t(max(int32_t(a), int32_t(b))); };
+constexpr auto fmin_bits = [](uint32_t a, uint32_t b) {
+  return __float_as_uint(fminf(__uint_as_float(a), __uint_as_float(b)));
+};
+constexpr auto fmax_bits = [](uint32_t a, uint32_t b) {
+  return __float_as_uint(fmaxf(__uint_as_float(a), __uint_as_float(b)));
+};
+constexpr auto umin_bits = [](uint32_t a, uint32_t b) { return min(a, b); };
+constexpr auto umax_bits = [](uint32_t a, uint32_t b) { return max(a, b); };
 
 struct Pick {
-  uint32_t digit, rem, cnt;
+  uint32_t digit, rem, cnt;   // cnt == 0: fewer than rem keys are counted
 };
 
 // Run by one whole wave: in a histogram of 64 * BPL bins searched from the highest bin down,
-// the bin holding the rem-th largest counted key (1 <= rem <= total), the rank left inside
-// it and its count; every lane receives the result.  Level 1: lane l sums bins
-// 64 BPL - BPL (l + 1) .. 64 BPL - 1 - BPL l and a wave scan finds the lane whose range
-// holds the rank; level 2: lane j < BPL reads that range's j-th highest bin and a second
-// scan finds the bin.
+// the bin holding the rem-th largest counted key (rem >= 1), the rank left inside it and its
+// count; every lane receives the result.  When all bins hold fewer, rem is what is left after
+// them.  Level 1: lane l sums bins 64 BPL - BPL (l + 1) .. 64 BPL - 1 - BPL l and a wave scan
+// finds the lane whose range holds the rank; level 2: lane j < BPL reads that range's j-th
+// highest bin and a second scan finds the bin.
 template <int BPL>
 __device__ __forceinline__ Pick pick_bucket(const uint32_t* h, uint32_t rem, int lane) {
   constexpr int NB = 64 * BPL;
+  static_assert(BPL % 4 == 0 && BPL <= 64, "16-byte reads, one bin a lane");
   const uint32_t* mine = h + NB - BPL * (lane + 1);
   uint32_t sum = 0u;
-  if constexpr (BPL % 4 == 0) {
 #pragma unroll
-    for (int q = 0; q < BPL / 4; ++q) {
-      const uint4 v = reinterpret_cast<const uint4*>(mine)[q];
-      sum += (v.x + v.y) + (v.z + v.w);
-    }
-  } else {
-#pragma unroll
-    for (int q = 0; q < BPL; ++q) sum += mine[q];
+  for (int q = 0; q < BPL / 4; ++q) {
+    const uint4 v = reinterpret_cast<const uint4*>(mine)[q];
+    sum += (v.x + v.y) + (v.z + v.w);
   }
   const uint32_t incl = wave_incl_scan(sum, lane);
   const uint64_t over = __ballot(incl >= rem);
-  const int owner = over ? int(__builtin_ctzll(over)) : 63;   // rem <= total: some lane does
+  if (over == 0) return {0u, rem - uint32_t(__builtin_amdgcn_readlane(int(incl), 63)), 0u};
+  const int owner = int(__builtin_ctzll(over));
   const uint32_t before = uint32_t(__builtin_amdgcn_readlane(int(incl - sum), owner));
   const int top = NB - BPL * owner - 1;              // the owner's highest bin
   const uint32_t c = lane < BPL ? h[top - lane] : 0u;
@@ -276,55 +160,60 @@ __device__ __forceinline__ Pick pick_bucket(const uint32_t* h, uint32_t rem, int
   return {uint32_t(top - j), rem - before - (ij - cj), cj};
 }
 
-// Ranks in index order of flagged keys: base[c] = flagged keys before this thread's part of
-// chunk c.  wtot: [RWAVES][RCH / 2] words of
-// LDS owned by this call (16-byte aligned rows); wave: the wave's index, uniform.  Contains
-// one barrier.  After it, lanes 0..15 of every wave scan the 16 waves' totals.
-static_assert(RPT == 32, "one bit per key in a 32-bit mask");
-static_assert(RWAVES == 16, "the waves' totals are combined in one row of 16 lanes");
-// own[q]: this thread's flagged keys in chunks 2q (low half) and 2q + 1 (high half).
-__device__ __forceinline__ void chunk_offsets(const uint32_t (&own)[RCH / 2], uint32_t (&base)[RCH],
-                                              uint32_t (*wtot)[RCH / 2], int lane, int wave) {
-  uint32_t inc[RCH / 2];
+template <int NT, int CH>
+struct KeepLds {
+  static constexpr int NW = NT / 64, NQ = (CH + 1) / 2;
+  static constexpr int DIGIT = NT < 1024 ? 9 : 11, NB = 1 << DIGIT;   // bins, and bits of a digit
+  static constexpr int NC = NT * CH * RCW < CMAX ? NT * CH * RCW : CMAX;
+  __attribute__((aligned(16))) uint32_t hist[NB];
+  __attribute__((aligned(16))) uint32_t cand[NC];
+  __attribute__((aligned(16))) uint32_t wtot[4][NW][NQ];
+  uint32_t red[4][NW];
+  uint32_t sh_key, sh_rem, sh_cnt, sh_ncand;
+};
+
+// Ranks in index order of flagged scores: base[c] = flagged scores before this thread's part of
+// chunk c, from `run` on, which moves on to the end of the tile.  own[q]: this thread's flagged
+// scores in chunks 2q (low half) and 2q + 1 (high half).  wtot: LDS owned by this call until the
+// second barrier from here; wave: the wave's index, uniform.  Contains one barrier.  After it,
+// lanes 0 .. NW - 1 of every wave scan the waves' totals.
+template <int NW, int CH, int NQ>
+__device__ __forceinline__ void chunk_offsets(const uint32_t (&own)[NQ], uint32_t (&base)[CH], uint32_t& run,
+                                              uint32_t (*wtot)[NQ], int lane, int wave) {
+  static_assert(NW <= 16, "the waves' totals are combined in one row of 16 lanes");
+  uint32_t inc[NQ], tv[NQ];
 #pragma unroll
-  for (int q = 0; q < RCH / 2; ++q) {
+  for (int q = 0; q < NQ; ++q) {
     // inclusive scan over the wave, two chunks per word (a field stays below 4 * 64 + 1)
     inc[q] = wave_incl_scan(own[q], lane);
   }
-  if (lane == 63) *reinterpret_cast<uint4*>(wtot[wave]) = make_uint4(inc[0], inc[1], inc[2], inc[3]);
-  __syncthreads();
-  uint4 t = make_uint4(0u, 0u, 0u, 0u);
-  if (lane < RWAVES) t = *reinterpret_cast<const uint4*>(wtot[lane]);
-  const uint32_t tv[4] = {t.x, t.y, t.z, t.w};
-  uint32_t run = 0u;
+  if (lane == 63) {
 #pragma unroll
-  for (int q = 0; q < RCH / 2; ++q) {
+    for (int q = 0; q < NQ; ++q) wtot[wave][q] = inc[q];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) tv[q] = lane < NW ? wtot[lane][q] : 0u;
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
     const uint32_t sc = row_scan(tv[q]);
-    const uint32_t all = uint32_t(__builtin_amdgcn_readlane(int(sc), RWAVES - 1));
+    const uint32_t all = uint32_t(__builtin_amdgcn_readlane(int(sc), NW - 1));
     const uint32_t bef = uint32_t(__builtin_amdgcn_readlane(int(sc - tv[q]), wave));
     const uint32_t mine = bef + inc[q] - own[q];
     base[2 * q] = run + (mine & 0xffffu);
     run += all & 0xffffu;
-    base[2 * q + 1] = run + (mine >> 16);
+    if (2 * q + 1 < CH) base[2 * q + 1 < CH ? 2 * q + 1 : 0] = run + (mine >> 16);
     run += all >> 16;
   }
 }
 
 // own[] of chunk_offsets from a mask (bit 4c + i: slot i of chunk c)
-__device__ __forceinline__ void chunk_counts(uint32_t m, uint32_t (&own)[RCH / 2]) {
+template <int NQ>
+__device__ __forceinline__ void chunk_counts(uint32_t m, uint32_t (&own)[NQ]) {
 #pragma unroll
-  for (int q = 0; q < RCH / 2; ++q)
+  for (int q = 0; q < NQ; ++q)
     own[q] = uint32_t(__popc((m >> (8 * q)) & 0xfu)) | (uint32_t(__popc((m >> (8 * q + 4)) & 0xfu)) << 16);
 }
-
-struct RegLds {
-  uint32_t hist[SBINS];
-  uint32_t cand[CMAX];
-  uint32_t whist[WBINS];
-  uint32_t red[5][RWAVES];
-  __attribute__((aligned(16))) uint32_t wtot[2][RWAVES][RCH / 2];
-  uint32_t sh_digit, sh_rem, sh_cnt, sh_ncand;
-};
 
 // The descriptor's fields in scalar registers (a descriptor picked from the kernel
 // arguments by the block index is otherwise not known to be uniform).
@@ -334,13 +223,20 @@ __device__ __forceinline__ int64_t uniform64(int64_t x) {
   return int64_t((uint64_t(hi) << 32) | lo);
 }
 
-__global__ __launch_bounds__(RNT, 1) void select_keep_regs(const float* __restrict__ scores,
-                                                           const SelSeg* __restrict__ segs,
-                                                           SelInline inl, int n_segs,
-                                                           int32_t* __restrict__ keep) {
-  __shared__ __attribute__((aligned(16))) RegLds L;
-  // Workgroups walk the segments (one per CU; the kernel's registers allow no second):
-  // the stores of one segment drain while the loads of the next are in flight.
+// Four scores at any multiple of four bytes.
+typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
+
+template <int NT, int CH, bool STREAM>
+__global__ __launch_bounds__(NT, 1) void select_keep_kernel(const float* __restrict__ scores,
+                                                            const SelSeg* __restrict__ segs, SelInline inl,
+                                                            int n_segs, int32_t* __restrict__ keep) {
+  typedef KeepLds<NT, CH> Lds;
+  constexpr int NW = Lds::NW, NQ = Lds::NQ, NB = Lds::NB, NC = Lds::NC, DIGIT = Lds::DIGIT;
+  constexpr int CHUNK = NT * RCW, TILE = CH * CHUNK, SPT = CH * RCW;
+  static_assert(SPT <= 32, "one bit per score in a 32-bit mask");
+  __shared__ Lds L;
+  // With more segments than workgroups each walks several: the stores of one segment drain
+  // while the loads of the next are in flight.
   for (int sgi = blockIdx.x; sgi < n_segs; sgi += gridDim.x) {
     // thread indices opaque per iteration: nothing derived from them is hoisted out of the loop
     int tid = threadIdx.x;
@@ -350,315 +246,293 @@ __global__ __launch_bounds__(RNT, 1) void select_keep_regs(const float* __restri
     SelSeg sg = seg_desc(inl, segs, sgi);
     sg.start = uniform64(sg.start);
     sg.out = uniform64(sg.out);
-    sg.len = __builtin_amdgcn_readfirstlane(sg.len);
-    sg.k = __builtin_amdgcn_readfirstlane(sg.k);
-    const int n = sg.len, k = sg.k;
+    const int n = __builtin_amdgcn_readfirstlane(sg.len), k = __builtin_amdgcn_readfirstlane(sg.k);
     int32_t* out = keep + sg.out;
     if (k <= 0) continue;
     if (k >= n) {
-      for (int i = tid; i < n; i += RNT) out[i] = i;
+      for (int i = tid; i < n; i += NT) out[i] = i;
       continue;
     }
-    // key[4c + i] = score c * RCHUNK + 4 * tid + i, read from a uniform base plus a 32-bit
-    // byte offset.  With a 16-byte aligned start and a length divisible by four, one 16-byte
-    // load per chunk (chunks past the end re-read the last four scores); otherwise four
-    // loads per chunk (indices past the end re-read the last score).  Keys past the end are
-    // marked padding below.
-    const char* sb = reinterpret_cast<const char*>(scores + sg.start);
-    uint32_t key[RPT];
-    int t4 = 4 * tid;
-    if ((reinterpret_cast<uintptr_t>(sb) & 15u) == 0u && (n & 3) == 0) {
+    const float* sp = scores + sg.start;
+    float f[SPT];
+    // Tile at score t0 into f; NaN past the end of the segment.  Loads stay inside the segment: a
+    // thread whose four scores straddle the end reads the last four and shifts them down.
+    auto load = [&](uint32_t t0) {
+      if (n < 4) {
 #pragma unroll
-      for (int c = 0; c < RCH; ++c) {
-        const uint32_t off = uint32_t(min(c * RCHUNK + t4, n - 4)) * 4u;
-        const uint4 v = *reinterpret_cast<const uint4*>(sb + off);
-        key[4 * c] = v.x;
-        key[4 * c + 1] = v.y;
-        key[4 * c + 2] = v.z;
-        key[4 * c + 3] = v.w;
+        for (int j = 0; j < SPT; ++j) f[j] = __uint_as_float(0x7fc00000u);
+#pragma unroll
+        for (int u = 0; u < RCW; ++u)
+          if (RCW * tid + u < n) f[u] = sp[RCW * tid + u];
+        return;
       }
-    } else {
+      uint32_t t4 = t0 + RCW * tid;
 #pragma unroll
-      for (int j = 0; j < RPT; ++j) {
-        const uint32_t off = uint32_t(min((j >> 2) * RCHUNK + t4 + (j & 3), n - 1)) * 4u;
-        key[j] = *reinterpret_cast<const uint32_t*>(sb + off);
+      for (int c = 0; c < CH; ++c) {
+        const f32x4_u v = *reinterpret_cast<const f32x4_u*>(sp + min(c * CHUNK + t4, uint32_t(n - 4)));
+#pragma unroll
+        for (int u = 0; u < RCW; ++u) f[RCW * c + u] = v[u];
       }
-    }
-    // Index arithmetic restarts from an opaque copy of 4*tid here and before the stores, so
-    // the compiler recomputes it instead of keeping 64 indices (and their compare masks)
-    // live across the kernel.  vbits: bit j set when key j lies inside the segment.
-    asm volatile("" : "+v"(t4));
-    uint32_t vbits = 0u;
+      asm volatile("" : "+v"(t4));
 #pragma unroll
-    for (int c = 0; c < RCH; ++c) {
-      // slots i < n - (c * RCHUNK + 4 tid) of chunk c hold scores
-      const int nv = min(max(n - c * RCHUNK - t4, 0), RCW);
-      vbits |= ((1u << nv) - 1u) << (RCW * c);
-    }
-    const bool whole = vbits == 0xffffffffu;   // every key of this thread lies inside the segment
-    auto valid = [&](int j) { return ((vbits >> j) & 1u) != 0u; };
+      for (int c = 0; c < CH; ++c) {
+        if (t0 + (c + 1) * CHUNK <= uint32_t(n)) continue;   // uniform: the chunk is whole
+        const int sh = int(c * CHUNK + t4 - uint32_t(n - 4));   // > 0: slot u holds the score of slot u - sh
+        const float nan = __uint_as_float(0x7fc00000u);
+        const float x1 = f[RCW * c + 1], x2 = f[RCW * c + 2], x3 = f[RCW * c + 3];
+        f[RCW * c] = sh <= 0 ? f[RCW * c] : sh == 1 ? x1 : sh == 2 ? x2 : sh == 3 ? x3 : nan;
+        f[RCW * c + 1] = sh <= 0 ? x1 : sh == 1 ? x2 : sh == 2 ? x3 : nan;
+        f[RCW * c + 2] = sh <= 0 ? x2 : sh == 1 ? x3 : nan;
+        f[RCW * c + 3] = sh <= 0 ? x3 : nan;
+      }
+    };
+    // pass(t0) for every tile, its scores in f
+    auto tiles = [&](auto&& pass) {
+      if constexpr (STREAM) {
+        for (uint32_t t0 = 0; t0 < uint32_t(n); t0 += TILE) {
+          load(t0);
+          pass(t0);
+        }
+      } else {
+        pass(0);
+      }
+    };
+    if constexpr (!STREAM) load(0);
 
-    // keys; their smallest, their largest (NaN detection) and the largest + FIN_SHIFT
-    int32_t mn = I32_MAX, mx = I32_MIN, mf = I32_MIN;
-    if (whole) {
+    // the finite scores' extremes
+    float mn = INFINITY, mx = -INFINITY;
+    tiles([&](uint32_t) {
 #pragma unroll
-      for (int j = 0; j < RPT; ++j) {
-        const int32_t s = skey(key[j]);
-        key[j] = uint32_t(s);
-        mn = min(mn, s);
-        mx = max(mx, s);
-        mf = max(mf, int32_t(uint32_t(s) + FIN_SHIFT));
+      for (int j = 0; j < SPT; ++j) {
+        const bool fin = fabsf(f[j]) < INFINITY;
+        mn = fminf(mn, fin ? f[j] : mn);
+        mx = fmaxf(mx, fin ? f[j] : mx);
       }
-    } else {
-#pragma unroll
-      for (int j = 0; j < RPT; ++j) {
-        const int32_t s = skey(key[j]);
-        key[j] = uint32_t(s);
-        const bool v = valid(j);
-        mn = v ? min(mn, s) : mn;
-        mx = v ? max(mx, s) : mx;
-        mf = v ? max(mf, int32_t(uint32_t(s) + FIN_SHIFT)) : mf;
-      }
-    }
+    });
+    __syncthreads();   // the segment before is done with the LDS
     {
-      const uint32_t r0 = wave_reduce(uint32_t(mn), uint32_t(I32_MAX), imin);
-      const uint32_t r1 = wave_reduce(uint32_t(mx), uint32_t(I32_MIN), imax);
-      const uint32_t r2 = wave_reduce(uint32_t(mf), uint32_t(I32_MIN), imax);
+      const uint32_t r0 = wave_reduce(__float_as_uint(mn), __float_as_uint(INFINITY), fmin_bits);
+      const uint32_t r1 = wave_reduce(__float_as_uint(mx), __float_as_uint(-INFINITY), fmax_bits);
       if (lane == 0) {
         L.red[0][wave] = r0;
         L.red[1][wave] = r1;
-        L.red[2][wave] = r2;
       }
     }
-    for (int i = tid; i < SBINS; i += RNT) L.hist[i] = 0u;
+    for (int i = tid; i < NB; i += NT) L.hist[i] = 0u;
     if (tid == 0) L.sh_ncand = 0u;
     __syncthreads();
-    mn = int32_t(row0_reduce(lane < RWAVES ? L.red[0][lane] : uint32_t(I32_MAX), uint32_t(I32_MAX), imin));
-    mx = int32_t(row0_reduce(lane < RWAVES ? L.red[1][lane] : uint32_t(I32_MIN), uint32_t(I32_MIN), imax));
-    mf = int32_t(row0_reduce(lane < RWAVES ? L.red[2][lane] : uint32_t(I32_MIN), uint32_t(I32_MIN), imax));
-    if (mn < KEY_NINF || mx > KEY_PINF) {
-      // some score is NaN: every NaN key becomes KEY_NAN and the extremes are taken again
-      // (KEY_NAN + FIN_SHIFT stays clear of INT_MIN)
-      mn = I32_MAX;
-      mf = I32_MIN;
+    mn = __uint_as_float(row0_reduce(lane < NW ? L.red[0][lane] : __float_as_uint(INFINITY),
+                                     __float_as_uint(INFINITY), fmin_bits));
+    mx = __uint_as_float(row0_reduce(lane < NW ? L.red[1][lane] : __float_as_uint(-INFINITY),
+                                     __float_as_uint(-INFINITY), fmax_bits));
+    const float inv = float(NB - 2) / (mx - mn);
+    // a product of 0 and infinity is NaN, which the clamp takes to 0
+    auto bin_of = [&](float x) { return uint32_t(fminf(fmaxf((x - mn) * inv, 0.f), float(NB - 1))); };
+
+    if (mn != mx) {
+      tiles([&](uint32_t) {
 #pragma unroll
-      for (int j = 0; j < RPT; ++j) {
-        int32_t s = int32_t(key[j]);
-        s = (s < KEY_NINF || s > KEY_PINF) ? KEY_NAN : s;
-        key[j] = uint32_t(s);
-        const bool v = valid(j);
-        mn = v ? min(mn, s) : mn;
-        mf = v ? max(mf, int32_t(uint32_t(s) + FIN_SHIFT)) : mf;
-      }
-      const uint32_t r0 = wave_reduce(uint32_t(mn), uint32_t(I32_MAX), imin);
-      const uint32_t r2 = wave_reduce(uint32_t(mf), uint32_t(I32_MIN), imax);
+        for (int j = 0; j < SPT; ++j)
+          if (f[j] == f[j]) atomicAdd(&L.hist[bin_of(f[j])], 1u);
+      });
+    } else {
+      // Equal finite scores share bin 0, where every lane's atomic would wait for all others: a wave
+      // adds them up first (eight segments of 32768 equal scores: 45 us by atomics alone, 20 us).
+      uint32_t zeros = 0u;
+      tiles([&](uint32_t) {
+#pragma unroll
+        for (int j = 0; j < SPT; ++j) {
+          if (f[j] == f[j]) {
+            const uint32_t b = bin_of(f[j]);
+            if (b == 0u)
+              ++zeros;
+            else
+              atomicAdd(&L.hist[b], 1u);
+          }
+        }
+      });
+      zeros = wave_reduce(zeros, 0u, [](uint32_t a, uint32_t b) { return a + b; });
+      if (lane == 0) atomicAdd(&L.hist[0], zeros);
+    }
+    __syncthreads();
+    if (wave == 0) {
+      const Pick p = pick_bucket<NB / 64>(L.hist, uint32_t(k), lane);
       if (lane == 0) {
-        L.red[3][wave] = r0;
-        L.red[4][wave] = r2;
+        L.sh_key = p.digit;
+        L.sh_rem = p.rem;
+        L.sh_cnt = p.cnt;
       }
-      __syncthreads();
-      mn = int32_t(row0_reduce(lane < RWAVES ? L.red[3][lane] : uint32_t(I32_MAX), uint32_t(I32_MAX), imin));
-      mf = int32_t(row0_reduce(lane < RWAVES ? L.red[4][lane] : uint32_t(I32_MIN), uint32_t(I32_MIN), imax));
     }
-    // From here on the registers hold rel = min(key - kmin, rcap): the order is unchanged and
-    // +inf keys (if any) equal rcap.  With no key below +inf, every rel is 0.  Padding
-    // (indices past the end) becomes rel 0, the smallest key: it is last in index order, and
-    // since k < n the kept ties (lowest index first) never reach it, so it changes no
-    // selection; counts below may include it.
-    const uint32_t kmin = uint32_t(mn);
-    const uint32_t rcap = mf != I32_MIN ? uint32_t(mf) - FIN_SHIFT - kmin + 1u : 0u;
-    if (whole) {
-#pragma unroll
-      for (int j = 0; j < RPT; ++j) key[j] = min(key[j] - kmin, rcap);
-    } else {
-#pragma unroll
-      for (int j = 0; j < RPT; ++j) key[j] = valid(j) ? min(key[j] - kmin, rcap) : 0u;
-    }
-
-    // T: the k-th largest rel; keep `rem` of the keys equal to T, of which there are `cnt`
-    // (a count that may include padding)
-    uint32_t rem = uint32_t(k), cnt;
-    uint32_t prefix = 0u;   // rel >> hi of the keys still in the running
-    const int B = rcap ? 32 - __clz(rcap) : 0;   // rel < 2^B
-    if (B == 0) {
-      cnt = uint32_t(n);   // every key is 0
-    } else {
-      int hi = B > SD ? B - SD : 0;
-      // Chunks wholly past the end hold only padding (rel 0): one thread counts them into
-      // bin 0 at once.  Key by key, every lane of such a load's keys would hit that one bin.
-#pragma unroll
-      for (int c = 0; c < RCH; ++c) {
-        if (c * RCHUNK < n) {
-#pragma unroll
-          for (int u = 0; u < RCW; ++u) atomicAdd(&L.hist[key[RCW * c + u] >> hi], 1u);
-        }
-      }
-      if (tid == 0 && n < RMAX) atomicAdd(&L.hist[0], uint32_t(RCHUNK * (RCH - (n + RCHUNK - 1) / RCHUNK)));
-      __syncthreads();
-      if (wave == 0) {
-        const Pick p = pick_bucket<SBINS / 64>(L.hist, rem, lane);
+    __syncthreads();
+    const uint32_t bin = L.sh_key;
+    uint32_t rem = L.sh_rem, cnt = L.sh_cnt;   // T is the rem-th largest of the bin's cnt scores
+    uint32_t T = 0u;                           // its order key
+    if (cnt != 0u) {
+      auto here = [&](float x) { return x == x && bin_of(x) == bin; };
+      // T by block-wide digits of key - kmin (scores that are all equal leave no digit); each(visit)
+      // visits this thread's keys of the bin
+      auto search = [&](auto&& each) {
+        uint32_t kmin = 0xffffffffu, kmax = 0u;
+        each([&](uint32_t key) {
+          kmin = min(kmin, key);
+          kmax = max(kmax, key);
+        });
+        const uint32_t r0 = wave_reduce(kmin, 0xffffffffu, umin_bits);
+        const uint32_t r1 = wave_reduce(kmax, 0u, umax_bits);
         if (lane == 0) {
-          L.sh_digit = p.digit;
-          L.sh_rem = p.rem;
-          L.sh_cnt = p.cnt;
-        }
-      }
-      __syncthreads();
-      prefix = L.sh_digit;
-      rem = L.sh_rem;
-      cnt = L.sh_cnt;
-      if (hi > 0 && cnt <= uint32_t(CMAX)) {
-        // The `cnt` keys of the chosen bucket (rel - cbase < 2^Lb) go to LDS as their low Lb
-        // bits.
-        const int Lb = hi;
-        const uint32_t cbase = prefix << Lb, width = 1u << Lb;
-#pragma unroll
-        for (int j = 0; j < RPT; ++j) {
-          // a key enters the list where it finds it (the finish needs no order); the
-          // increments of one instruction are combined by a single lane
-          const uint32_t d = key[j] - cbase;
-          if (d < width) {
-            const uint32_t pos = atomicAdd(&L.sh_ncand, 1u);
-            if (pos < uint32_t(CMAX)) L.cand[pos] = d;
-          }
+          L.red[2][wave] = r0;
+          L.red[3][wave] = r1;
         }
         __syncthreads();
-        if (wave == 0) {
-          // radix passes of WD bits over the list, by this wave alone: its LDS operations
-          // execute in program order, so the clears, the atomics and the reads of whist
-          // need no barrier (the waits and fences keep the compiler from moving them)
-          const int nc = int(min(cnt, uint32_t(CMAX)));
-          uint32_t p2 = 0u, r2 = rem, c2 = cnt;
-          int h2 = Lb;
-          while (h2 > 0) {
-            const int l2 = h2 > WD ? h2 - WD : 0;
-            const uint32_t m2 = (1u << (h2 - l2)) - 1u;
-#pragma unroll
-            for (int q = 0; q < WBINS / 64; ++q) L.whist[WBINS / 64 * lane + q] = 0u;
-            asm volatile("" ::: "memory");
-            // eight reads in flight before their atomics: the list is walked at LDS
-            // throughput rather than one read latency per element
-            for (int i0 = 0; i0 < nc; i0 += 8 * 64) {
-              uint32_t vv[8];
-#pragma unroll
-              for (int u = 0; u < 8; ++u) vv[u] = L.cand[min(i0 + u * 64 + lane, CMAX - 1)];
-#pragma unroll
-              for (int u = 0; u < 8; ++u)
-                if (i0 + u * 64 + lane < nc && (vv[u] >> h2) == p2)
-                  atomicAdd(&L.whist[(vv[u] >> l2) & m2], 1u);
+        kmin = row0_reduce(lane < NW ? L.red[2][lane] : 0xffffffffu, 0xffffffffu, umin_bits);
+        kmax = row0_reduce(lane < NW ? L.red[3][lane] : 0u, 0u, umax_bits);
+        int hi = kmax > kmin ? 32 - __clz(kmax - kmin) : 0;   // offsets < 2^hi
+        uint32_t prefix = 0u;                                 // offset >> hi of those in the running
+        while (hi > 0) {
+          // clear the histogram (the pick before read it before the barrier that ended it)
+          for (int i = tid; i < NB; i += NT) L.hist[i] = 0u;
+          __syncthreads();
+          const int lo = hi > DIGIT ? hi - DIGIT : 0;
+          const uint32_t dmask = (1u << (hi - lo)) - 1u;
+          each([&](uint32_t key) {
+            const uint32_t off = key - kmin;
+            if ((hi == 32 ? 0u : off >> (hi & 31)) == prefix) atomicAdd(&L.hist[(off >> lo) & dmask], 1u);
+          });
+          __syncthreads();
+          if (wave == 0) {
+            const Pick p = pick_bucket<NB / 64>(L.hist, rem, lane);
+            if (lane == 0) {
+              L.sh_key = p.digit;
+              L.sh_rem = p.rem;
+              L.sh_cnt = p.cnt;
             }
-            __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
-            asm volatile("" ::: "memory");
-            const Pick pk = pick_bucket<WBINS / 64>(L.whist, r2, lane);
-            __builtin_amdgcn_s_waitcnt(0xc07f);
-            asm volatile("" ::: "memory");
-            p2 = (p2 << (h2 - l2)) | pk.digit;
-            r2 = pk.rem;
-            c2 = pk.cnt;
-            h2 = l2;
           }
-          if (lane == 0) {
-            L.sh_digit = p2;
-            L.sh_rem = r2;
-            L.sh_cnt = c2;
-          }
+          __syncthreads();
+          prefix = (prefix << (hi - lo)) | L.sh_key;
+          rem = L.sh_rem;
+          cnt = L.sh_cnt;
+          hi = lo;
         }
-        __syncthreads();
-        prefix = (prefix << Lb) | L.sh_digit;
-        rem = L.sh_rem;
-        cnt = L.sh_cnt;
-        hi = 0;
-      }
-      while (hi > 0) {
-        // another block-wide digit over the keys whose bits above hi equal prefix: clear the
-        // histogram (the pick above read it before the barrier that ended it)
-        for (int i = tid; i < SBINS; i += RNT) L.hist[i] = 0u;
-        __syncthreads();
-        const int lo = hi > SD ? hi - SD : 0;
-        const uint32_t dmask = (1u << (hi - lo)) - 1u;
+        T = kmin + prefix;
+      };
+      if (cnt <= uint32_t(NC)) {
+        tiles([&](uint32_t) {
 #pragma unroll
-        for (int j = 0; j < RPT; ++j) {
-          const uint32_t rel = key[j];
-          if ((rel >> hi) == prefix) atomicAdd(&L.hist[(rel >> lo) & dmask], 1u);
-          __builtin_amdgcn_sched_barrier(0);   // one key at a time: no 32 live masks
-        }
-        __syncthreads();
-        if (wave == 0) {
-          const Pick p = pick_bucket<SBINS / 64>(L.hist, rem, lane);
-          if (lane == 0) {
-            L.sh_digit = p.digit;
-            L.sh_rem = p.rem;
-            L.sh_cnt = p.cnt;
+          for (int j = 0; j < SPT; ++j) {
+            // a score enters the list where it finds it (the search needs no order); the
+            // increments of one instruction are combined by a single lane
+            if (here(f[j])) {
+              const uint32_t pos = atomicAdd(&L.sh_ncand, 1u);
+              if (pos < uint32_t(NC)) L.cand[pos] = order_key(f[j]);
+            }
+            __builtin_amdgcn_sched_barrier(0);   // one score at a time: no 32 live masks
           }
-        }
+        });
         __syncthreads();
-        prefix = (prefix << (hi - lo)) | L.sh_digit;
-        rem = L.sh_rem;
-        cnt = L.sh_cnt;
-        hi = lo;
+        if (cnt <= RANK) {
+          if (uint32_t(tid) < cnt) {
+            const uint32_t mine = L.cand[tid];
+            uint32_t above = 0u, same = 0u;
+            for (uint32_t i = 0; i < cnt; i += 4) {
+              const uint4 v = *reinterpret_cast<const uint4*>(&L.cand[i]);
+              const uint32_t x[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+              for (uint32_t u = 0; u < 4; ++u) {
+                above += uint32_t(i + u < cnt && x[u] > mine);
+                same += uint32_t(i + u < cnt && x[u] == mine);
+              }
+            }
+            if (above < rem && rem <= above + same) {   // one value; its holders write the same
+              L.sh_key = mine;
+              L.sh_rem = rem - above;
+              L.sh_cnt = same;
+            }
+          }
+          __syncthreads();
+          T = L.sh_key;
+          rem = L.sh_rem;
+          cnt = L.sh_cnt;
+        } else {
+          const uint32_t nc = min(cnt, uint32_t(NC));
+          search([&](auto&& visit) {
+            for (uint32_t i = tid; i < nc; i += NT) visit(L.cand[i]);
+          });
+        }
+      } else if constexpr (NC < TILE || STREAM) {
+        search([&](auto&& visit) {
+          tiles([&](uint32_t) {
+#pragma unroll
+            for (int j = 0; j < SPT; ++j) {
+              if (here(f[j])) visit(order_key(f[j]));
+              __builtin_amdgcn_sched_barrier(0);   // one score at a time: no 32 live masks
+            }
+          });
+        });
       }
     }
-    const uint32_t T = prefix;
-    // every tie is kept when their count equals the number still to keep (a count that
-    // includes padding cannot: real ties alone already reach rem); keys >= T1 are kept
-    // outright
-    const bool all_ties = cnt == rem;
-    const uint32_t T1 = all_ties ? T : T + 1u;
-
-    uint32_t take = 0u, own[RCH / 2];
-    uint32_t base[RCH];
-    if (all_ties) {
-      // kept: the keys >= T1, counted per chunk (no mask: the stores compare again)
-      uint32_t cc[RCH];
+    // T == 0: the threshold is NaN; every other score is above it, and rem of the NaNs are kept
+    // (the NaNs past the end come last in index order, and k < n leaves them out).
+    const bool t_nan = T == 0u;
+    const float tf = key_float(T);
+    auto above = [&](float x) { return t_nan ? x == x : x > tf; };
+    auto tie = [&](float x) { return t_nan ? x != x : x == tf; };
+    const bool all_ties = !t_nan && cnt == rem;   // every tie is kept
+    // stores go through a descriptor that drops any past the budget
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(out, 0, STREAM ? 0 : 4 * k, 0x00020000);
+    uint32_t ties = 0u, kept = 0u;   // in the tiles before
+    int par = 0;
+    tiles([&](uint32_t t0) {
+      uint32_t take = 0u, own[NQ], base[CH];
+      if (all_ties) {
 #pragma unroll
-      for (int c = 0; c < RCH; ++c) {
-        cc[c] = 0u;
+        for (int j = SPT - 1; j >= 0; --j) take = (take << 1) | uint32_t(f[j] >= tf);
+      } else {
+        // ties ranked in index order; the first rem are kept
+        uint32_t eq = 0u;
 #pragma unroll
-        for (int u = 0; u < RCW; ++u) cc[c] += uint32_t(key[RCW * c + u] >= T1);
-      }
+        for (int j = SPT - 1; j >= 0; --j) {
+          take = (take << 1) | uint32_t(above(f[j]));
+          eq = (eq << 1) | uint32_t(tie(f[j]));
+        }
+        chunk_counts(eq, own);
+        chunk_offsets<NW, CH, NQ>(own, base, ties, L.wtot[2 + par], lane, wave);
 #pragma unroll
-      for (int q = 0; q < RCH / 2; ++q) own[q] = cc[2 * q] | (cc[2 * q + 1] << 16);
-    } else {
-      // ties ranked in index order; the first rem are kept
-      uint32_t eq = 0u;
-#pragma unroll
-      for (int j = RPT - 1; j >= 0; --j) {
-        take = (take << 1) | uint32_t(key[j] >= T1);
-        eq = (eq << 1) | uint32_t(key[j] == T);
-      }
-      chunk_counts(eq, own);
-      chunk_offsets(own, base, L.wtot[0], lane, wave);
-#pragma unroll
-      for (int j = 0; j < RPT; ++j) {
-        const uint32_t below = uint32_t(__popc(eq & (((1u << (j & 3)) - 1u) << (j & ~3))));
-        take |= uint32_t(((eq >> j) & 1u) && base[j >> 2] + below < rem) << j;
+        for (int j = 0; j < SPT; ++j) {
+          const uint32_t below = uint32_t(__popc(eq & (((1u << (j & 3)) - 1u) << (j & ~3))));
+          take |= uint32_t(((eq >> j) & 1u) && base[j >> 2] + below < rem) << j;
+        }
       }
       chunk_counts(take, own);
-    }
-    chunk_offsets(own, base, L.wtot[1], lane, wave);
-    int t4s = 4 * tid;
-    asm volatile("" : "+v"(t4s));
-    // kept keys of chunk c at ranks base[c], base[c] + 1, ...; the descriptor's bound (the
-    // budget) drops any store past it
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(out, 0, 4 * k, 0x00020000);
-    auto emit = [&](auto kept) {
+      chunk_offsets<NW, CH, NQ>(own, base, kept, L.wtot[par], lane, wave);
+      par ^= 1;
+      uint32_t t4 = t0 + RCW * tid;
+      asm volatile("" : "+v"(t4));
+      // kept scores of chunk c at ranks base[c], base[c] + 1, ...
 #pragma unroll
-      for (int c = 0; c < RCH; ++c) {
-        uint32_t r = 4u * base[c];
+      for (int c = 0; c < CH; ++c) {
+        uint32_t r = base[c];
 #pragma unroll
         for (int u = 0; u < RCW; ++u) {
-          if (kept(RCW * c + u)) {
-            __builtin_amdgcn_raw_buffer_store_b32(uint32_t(c * RCHUNK + t4s + u), rs, int(r), 0, 0);
-            r += 4u;
+          if ((take >> (RCW * c + u)) & 1u) {
+            const uint32_t i = c * CHUNK + t4 + u;
+            if constexpr (STREAM) {   // a budget may exceed a descriptor's 4 GB
+              if (r < uint32_t(k)) out[r] = int32_t(i);
+            } else {
+              __builtin_amdgcn_raw_buffer_store_b32(i, rs, int(4u * r), 0, 0);
+            }
+            ++r;
           }
         }
       }
-    };
-    if (all_ties)
-      emit([&](int j) { return key[j] >= T1; });
-    else
-      emit([&](int j) { return ((take >> j) & 1u) != 0u; });
+    });
   }
+}
+
+template <int NT, int CH, bool STREAM>
+void launch_keep(const float* scores, const SelSeg* segs, const SelInline& inl, int n_segs, int grid,
+                 int32_t* keep, hipStream_t s) {
+  hipLaunchKernelGGL((select_keep_kernel<NT, CH, STREAM>), dim3(grid), dim3(NT), 0, s, scores, segs, inl, n_segs,
+                     keep);
 }
 
 }  // namespace
@@ -689,19 +563,25 @@ hipError_t launch_select(const float* scores, const SelSeg* segs_h, const SelSeg
     inl.len = segs_h[0].len;
     inl.k = segs_h[0].k;
   }
-  // The register path pays a fixed cost per segment (its passes and scans are a chain of
-  // block-wide barriers) that the re-reading kernel does not; it wins once a segment is
-  // long enough for the repeated reads to dominate.
-  if (max_len > 8192 && max_len <= RMAX) {
+  // The smallest kernel that holds the longest segment in registers: each further chunk costs a
+  // short segment instructions and barriers (8000 scores: 8.7 us in two chunks, 12.5 us in eight).
+  if (max_len <= 256 * RCW)
+    launch_keep<256, 1, false>(scores, segs_d, inl, n_segs, n_segs, keep, s);
+  else if (max_len <= RNT * RCW)
+    launch_keep<RNT, 1, false>(scores, segs_d, inl, n_segs, n_segs, keep, s);
+  else if (max_len <= 2 * RNT * RCW)
+    launch_keep<RNT, 2, false>(scores, segs_d, inl, n_segs, n_segs, keep, s);
+  else {
     // one workgroup per CU of the current device, each walking segments
     int dev = 0, cus = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(select_keep_regs, dim3(std::min(n_segs, std::max(cus, 1))), dim3(RNT), 0, s, scores,
-                       segs_d, inl, n_segs, keep);
-  } else {
-    hipLaunchKernelGGL(select_keep_kernel, dim3(n_segs), dim3(SNT), 0, s, scores, segs_d, inl, keep);
+    const int grid = std::min(n_segs, std::max(cus, 1));
+    if (max_len <= 8 * RNT * RCW)
+      launch_keep<RNT, 8, false>(scores, segs_d, inl, n_segs, grid, keep, s);
+    else
+      launch_keep<RNT, 8, true>(scores, segs_d, inl, n_segs, grid, keep, s);
   }
   return hipGetLastError();
 }

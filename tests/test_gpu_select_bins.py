@@ -1,0 +1,79 @@
+"""Keep selection where its kernel changes: the sizes at which the next kernel takes over (1024,
+4096, 8192 and 32768 scores), the loads at the end of a segment (1 to 3 scores left, any start), and
+inputs that fill the threshold's bin beyond the ranked list (256), beyond the gathered list
+(4096), with equal scores, with NaN as the threshold and with ranges that overflow or vanish."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _reference(s, k):
+    """The k first under (score descending, NaN last, lower index first), in index order."""
+    key = np.where(np.isnan(s), -np.inf, s.astype(np.float64))
+    order = np.lexsort((np.arange(len(s)), -key, np.isnan(s)))
+    return np.sort(order[:k]).astype(np.int32)
+
+
+def _check(segs, fractions, lead=0):
+    from paper_2607_27600_amd import cc
+    s = np.concatenate([np.zeros(lead, np.float32)] + segs).astype(np.float32)
+    lens = [len(x) for x in segs]
+    starts = [lead + sum(lens[:i]) for i in range(len(lens))]
+    dev = torch.from_numpy(s).cuda()
+    for frac in fractions:
+        ks = [min(n, max(1, int(frac * n))) for n in lens]
+        keep = torch.full((sum(ks),), -7, dtype=torch.int32, device="cuda")
+        cc.cc_select_keep(dev, starts, lens, ks, keep)
+        got, off = keep.cpu().numpy(), 0
+        for x, k in zip(segs, ks):
+            np.testing.assert_array_equal(got[off:off + k], _reference(x, k), err_msg=f"len={len(x)} k={k}")
+            off += k
+
+
+@pytest.mark.parametrize("n", [2, 3, 4, 5, 255, 1023, 1024, 1025, 1026, 4095, 4096, 4097, 8191, 8192, 8193,
+                               32767, 32768, 32769, 32770, 65536, 98307, 131072])
+def test_sizes(n):
+    print(f"[select] n={n}", flush=True)
+    r = np.random.default_rng(n)
+    for lead in (0, 1, 2, 3):
+        x = np.maximum(r.standard_normal(n) * 2.5 + 9.0, 0.0).astype(np.float32)
+        x[-1] = np.inf
+        _check([x], (0.0, 0.125, 2 / 3, 1 - 1.0 / n), lead)
+
+
+def _hostile(kind, n):
+    r = np.random.default_rng(n + len(kind))
+    x = (r.standard_normal(n) * 2.5 + 9.0).astype(np.float32)
+    if kind == "equal":
+        x[:] = 11.75
+    elif kind == "equal and infinite":
+        x = np.where(r.random(n) < 0.3, np.float32(np.inf), np.where(r.random(n) < 0.3, np.float32(-np.inf),
+                                                                     np.float32(11.75)))
+    elif kind == "nan":
+        x[r.random(n) < 0.6] = np.nan
+    elif kind == "only infinite":
+        x = np.where(r.random(n) < 0.5, np.float32(np.inf), np.float32(-np.inf))
+        x[::9] = np.nan
+    elif kind == "overflowing range":
+        x = (r.uniform(-1, 1, n) * 3.4e38).astype(np.float32)
+    elif kind == "denormal":
+        x = (r.integers(-3, 4, n) * np.float32(1e-45)).astype(np.float32)
+    elif kind == "zeros":
+        x[r.random(n) < 0.7] = 0.0
+        x[::3] = -0.0
+    elif kind == "narrow band":   # thousands of different scores in one bin
+        x = (11.0 + r.uniform(0.0, 1e-3, n)).astype(np.float32)
+        x[::50] = r.uniform(0.0, 100.0, len(x[::50]))
+    else:                         # some hundreds in one bin
+        x = np.where(np.arange(n) % 8 == 0, 11.0 + r.uniform(0.0, 1e-3, n), x).astype(np.float32)
+    return x.astype(np.float32)
+
+
+@pytest.mark.parametrize("kind", ["equal", "equal and infinite", "nan", "only infinite", "overflowing range", "denormal",
+                                  "zeros", "narrow band", "cluster"])
+def test_hostile_scores(kind):
+    for n in (1000, 4001, 8000, 32768, 50001):
+        print(f"[select] {kind} n={n}", flush=True)
+        _check([_hostile(kind, n), _hostile(kind, n // 2)], (0.0, 0.2, 0.5, 0.9))
