@@ -132,8 +132,8 @@ __device__ __forceinline__ void page_numbers(const int32_t* p0, const int32_t* p
 // KS key groups of four waves share an item's rows: group kg takes key tiles tb + kg, tb + kg +
 // KS, ... through buffers of its own, and the groups' (max, sum, output) merge through LDS at
 // the end.  KS = 1 is the kernel described above.  KS = 2 halves the serial chain of tiles of an
-// item and is for launches of at most one item a CU, where a workgroup has its CU to itself and
-// each SIMD only one wave, with at least 12 tiles to share: one group against two, 8 heads of 128
+// item and is for launches of few items with tiles to share, whose length is that of one chain
+// (launch_attention has the rule): one group against two, 8 heads of 128
 // on one KV head: 1500 entries 29.7 and 26.6 us, 3000 entries 53 and 45; 8 heads of 64, 3000
 // entries 45 and 34.5; 28 heads of 128 on four KV heads: 900 entries 23.3 and 22.1, 512 entries
 // 15.2 and 15.6 (each tile costs a shared CU more, and the merge is a barrier).
@@ -623,8 +623,14 @@ hipError_t launch_attention(const AttnLaunch& a, hipStream_t s) {
   if (a.dtype != CC_BF16) return launch_attention_f32(a, s);
   // a table stands for more than ATTN_INLINE sequences: many items
   if (a.items.table) return launch_bf16<1>(a, a.items, s);
-  // two key groups: at most one item a CU and tiles to share (figures at the kernel)
-  const bool split = a.n_work <= 256 && a.items.seqs[0].n >= 12 * BN;
+  // Two key groups where the longest chain of tiles, not the sum of all, makes the launch's length:
+  // up to one item a CU (two groups fill it) from 12 tiles on, up to two items a CU (one group each
+  // would fill it, but the short ones leave early) from 12 to 28 tiles on.  One group against two:
+  // 264 items of up to 66 tiles 57.4 and 45.3 us (64 wide), 288 of 36 49.6 and 41.5 (128 wide), 504
+  // of 36 58.6 and 54.5, 512 of 64 66.9 and 52.0 (64 wide); but 440 of 16 32.3 and 35.3, 352 of 11
+  // 16.1 and 18.5, and beyond: 552 of 24 45.3 and 49.7, 660 of 32 38.9 and 43.3.
+  const int tiles = a.items.seqs[0].n / BN;
+  const bool split = a.n_work <= 512 && 16 * tiles >= 16 * 12 + (a.n_work > 256 ? a.n_work - 256 : 0);
   if (a.items.n_seqs == 1) {
     const AttnOne one{a.items.nkv, a.items.seqs[0].n};
     return split ? launch_bf16<2>(a, one, s) : launch_bf16<1>(a, one, s);

@@ -1,5 +1,5 @@
 """Attention where its launch changes: work items found from up to 16 sequences by value and from
-the uploaded table beyond, and two key groups a workgroup for launches of at most 256 items (one
+the uploaded table beyond, and two key groups a workgroup for launches of few items (up to 256, and up to 512 with long chains; one
 tile, an odd and an even number of tiles, sequences with no key at all)."""
 import numpy as np
 import pytest
@@ -17,6 +17,8 @@ pytestmark = pytest.mark.gpu
     (tuple(range(99, 3, -6)) + (40,), 2, 2, 128, True),    # 17: the table
     ((700, 100, 701, 0, 1), 32, 8, 128, False),            # more than 256 items
     ((513,), 28, 4, 128, False),
+    ((1800, 700, 0, 65, 1), 14, 2, 64, True),              # 284 items of up to 29 tiles: two groups
+    ((1530, 1), 28, 4, 128, False),                        # 340 items of up to 24 tiles
 ])
 @pytest.mark.parametrize("diag", ["strict", "inclusive"])
 def test_bf16(lens, hq, hkv, d, paged, diag):
