@@ -363,10 +363,8 @@ cc_status score_full(const cc_problem* p, const cc_inputs* in, float* scores, vo
   void* o = at(ws, L.o);
   void* act = at(ws, L.act);
   float* part = reinterpret_cast<float*>(at(ws, L.part));
-  CC_HIP(launch_rope_table(in->pos_ids, p->cu_seqlens_d, p->n_seqs, rot, N, p->head_dim,
-                           double(p->rope_theta), s));
-  CC_HIP(launch_embed(in->embed, in->token_ids, h, N, D, s));
-  CC_HIP(launch_residual_rmsnorm(nullptr, 0, h, in->layers_h[0].attn_norm, a, N, D, p->rms_eps, s));
+  CC_HIP(launch_enter(in->embed, in->token_ids, in->pos_ids, p->cu_seqlens_d, p->n_seqs, rot, h,
+                      in->layers_h[0].attn_norm, a, N, D, p->head_dim, double(p->rope_theta), p->rms_eps, s));
   for (int l = 0; l < p->n_layers; ++l) {
     const cc_layer_weights& W = in->layers_h[l];
     const void* next = l + 1 < p->n_layers ? in->layers_h[l + 1].attn_norm : in->final_norm;
@@ -411,10 +409,9 @@ cc_status score_last_h(const cc_problem* p, const cc_inputs* in, float* scores, 
   void* act = at(ws, L.act);
   float* part = reinterpret_cast<float*>(at(ws, L.part));
   const cc_layer_weights& W = in->layers_h[0];
-  CC_HIP(launch_rope_table(in->pos_ids, p->cu_seqlens_d, p->n_seqs, rot, N, p->head_dim,
-                           double(p->rope_theta), s));
-  CC_HIP(launch_embed(in->h_last, nullptr, h, N, D, s));   // widen H to the fp32 stream
-  CC_HIP(launch_residual_rmsnorm(nullptr, 0, h, W.attn_norm, a, N, D, p->rms_eps, s));
+  // H widens to the fp32 stream
+  CC_HIP(launch_enter(in->h_last, nullptr, in->pos_ids, p->cu_seqlens_d, p->n_seqs, rot, h, W.attn_norm, a, N,
+                      D, p->head_dim, double(p->rope_theta), p->rms_eps, s));
   CC_HIP(launch_qproj_rope(W.wq, a, q, rot, N, D, HD, s));
   CC_TRY(run_attention(p, q, &in->kv, in->kv.n_layers - 1, o, at(ws, L.attn), s));
   CC_HIP(launch_linear_residual_norm(o, W.wo, h, W.mlp_norm, a, N, D, HD, p->rms_eps, part, s));

@@ -269,15 +269,14 @@ hipError_t launch_linear_residual_norm(const void* x, const void* w, float* h, c
 // act[n][f] = silu(W_gate b[n])[f] * (W_up b[n])[f].
 hipError_t launch_gate_up_swiglu(const void* w_gate, const void* w_up, const void* b, void* act,
                                  int N, int D, int F, hipStream_t s);
-// h[n][:] = embed[ids[n]][:] (bf16 -> fp32); ids == null widens row n of `embed`.
-hipError_t launch_embed(const void* embed, const int32_t* ids, float* h, int N, int D,
-                        hipStream_t s);
+// The start of a pass: h[n][:] = embed[ids[n]][:] (bf16 -> fp32; ids == null widens row n of
+// `embed`), y = RMSNorm(h) with gain gamma, and rot[n][e] = (cos, sin)(pos[n] * theta^(-2e/head_dim)),
+// e < head_dim/2, computed in fp64 (pos == null: positions 0..n_b-1 within each sequence).
+hipError_t launch_enter(const void* embed, const int32_t* ids, const int32_t* pos, const int32_t* cu,
+                        int n_seqs, float2* rot, float* h, const void* gamma, void* y, int N, int D,
+                        int head_dim, double theta, float eps, hipStream_t s);
 // y[n][:] = bf16(h[n][:] / sqrt(mean(h[n]^2) + eps) * gamma), after h += part[0] + ... +
 // part[S-1] (each [N][D]) when part is not null.
 hipError_t launch_residual_rmsnorm(const float* part, int S, float* h, const void* gamma, void* y,
                                    int N, int D, float eps, hipStream_t s);
-// rot[n][e] = (cos, sin)(pos[n] * theta^(-2e/head_dim)), e < head_dim/2, computed in fp64.
-// pos == null: positions 0..n_b-1 within each sequence.
-hipError_t launch_rope_table(const int32_t* pos, const int32_t* cu, int n_seqs, float2* rot,
-                             int N, int head_dim, double theta, hipStream_t s);
 }  // namespace cc
