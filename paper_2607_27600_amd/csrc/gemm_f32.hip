@@ -35,13 +35,13 @@ __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
 // y[m][n], M = entries, N = output features.
 struct EpiStoreF {
   float* out;
-  template <int NB>
-  __device__ void operator()(const f32x4 (&acc)[NB][NB], const GemmArgsF& g, int tm, int m0w,
+  template <int MB, int NB>
+  __device__ void operator()(const f32x4 (&acc)[MB][NB], const GemmArgsF& g, int tm, int m0w,
                              int n0w, int lane, float* lds) const {
     (void)tm;
     (void)lds;
 #pragma unroll
-    for (int i = 0; i < NB; ++i)
+    for (int i = 0; i < MB; ++i)
 #pragma unroll
       for (int j = 0; j < NB; ++j) {
         const int n = n0w + j * 16 + (lane & 15);
@@ -67,9 +67,10 @@ struct EpiLseF {
   float2* partial;
   float* target;
   const int32_t* ids;
-  template <int NB>
-  __device__ void operator()(const f32x4 (&acc)[NB][NB], const GemmArgsF& g, int tm, int m0w,
+  template <int MB, int NB>
+  __device__ void operator()(const f32x4 (&acc)[MB][NB], const GemmArgsF& g, int tm, int m0w,
                              int n0w, int lane, float* lds) const {
+    static_assert(32 * MB == LMT, "one tile, one partial");
     constexpr int T = 32 * NB;
     const int grp = lane >> 4, c16 = lane & 15, wave = threadIdx.x >> 6;
     float2* red = reinterpret_cast<float2*>(lds);   // [2][T]
@@ -79,13 +80,13 @@ struct EpiLseF {
       const int id = n < g.N ? ids[n] : -1;
       float mx = -INFINITY, sm = 0.f;
 #pragma unroll
-      for (int i = 0; i < NB; ++i)
+      for (int i = 0; i < MB; ++i)
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           if (m0w + i * 16 + 4 * grp + e < g.M) mx = fmaxf(mx, acc[i][j][e]);
       const float ref = mx == -INFINITY ? 0.f : mx;   // a lane without rows, or of -inf logits, adds 0
 #pragma unroll
-      for (int i = 0; i < NB; ++i)
+      for (int i = 0; i < MB; ++i)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int m = m0w + i * 16 + 4 * grp + e;
@@ -112,19 +113,19 @@ struct EpiLseF {
   }
 };
 
-// T = 32 NB: 64 or 32.
-template <int NB, class Epi>
+// Tiles of 32 MB x 32 NB.
+template <int MB, int NB, class Epi>
 __global__ __launch_bounds__(256) void gemm_tn_f32(GemmArgsF g, Epi epi) {
-  constexpr int T = 32 * NB, LPT = T * FK / 4 / 256;   // float4 per thread per operand tile
-  __shared__ __attribute__((aligned(16))) float lds[2 * T * FLD];
+  constexpr int TM = 32 * MB, TN = 32 * NB;   // MB, NB: also the float4 a thread loads of each operand
+  __shared__ __attribute__((aligned(16))) float lds[(TM + TN) * FLD];
   float* As = lds;
-  float* Bs = lds + T * FLD;
+  float* Bs = lds + TM * FLD;
   const int tm = blockIdx.x / g.tiles_n, tn = blockIdx.x % g.tiles_n;
-  const int m0 = tm * T, n0 = tn * T;
+  const int m0 = tm * TM, n0 = tn * TN;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int grp = lane >> 4, r16 = lane & 15;
   const int wm = wave >> 1, wn = wave & 1;
-  float4 ra[LPT], rb[LPT];
+  float4 ra[MB], rb[NB];
   auto load1 = [&](const float* X, int row, int rows, int k) {
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
     if (row >= rows) return v;
@@ -141,38 +142,37 @@ __global__ __launch_bounds__(256) void gemm_tn_f32(GemmArgsF g, Epi epi) {
   };
   auto load = [&](int k0) {
 #pragma unroll
-    for (int i = 0; i < LPT; ++i) {
-      const int r = (i * 256 + tid) >> 3, c = (tid & 7) * 4;
-      ra[i] = load1(g.A, m0 + r, g.M, k0 + c);
-      rb[i] = load1(g.B, n0 + r, g.N, k0 + c);
-    }
-  };
-  f32x4 acc[NB][NB];
+    for (int i = 0; i < MB; ++i) ra[i] = load1(g.A, m0 + ((i * 256 + tid) >> 3), g.M, k0 + (tid & 7) * 4);
 #pragma unroll
-  for (int i = 0; i < NB; ++i)
+    for (int i = 0; i < NB; ++i) rb[i] = load1(g.B, n0 + ((i * 256 + tid) >> 3), g.N, k0 + (tid & 7) * 4);
+  };
+  f32x4 acc[MB][NB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
 #pragma unroll
     for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{};
   load(0);
   for (int k0 = 0; k0 < g.K; k0 += FK) {
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < LPT; ++i) {
-      const int r = (i * 256 + tid) >> 3, c = (tid & 7) * 4;
-      *reinterpret_cast<float4*>(As + r * FLD + c) = ra[i];
-      *reinterpret_cast<float4*>(Bs + r * FLD + c) = rb[i];
-    }
+    for (int i = 0; i < MB; ++i)
+      *reinterpret_cast<float4*>(As + ((i * 256 + tid) >> 3) * FLD + (tid & 7) * 4) = ra[i];
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+      *reinterpret_cast<float4*>(Bs + ((i * 256 + tid) >> 3) * FLD + (tid & 7) * 4) = rb[i];
     __syncthreads();
     if (k0 + FK < g.K) load(k0 + FK);
 #pragma unroll
     for (int ks = 0; ks < FK / 16; ++ks) {
-      float4 fa[NB], fb[NB];
+      float4 fa[MB], fb[NB];
 #pragma unroll
-      for (int i = 0; i < NB; ++i) {
-        fa[i] = *reinterpret_cast<const float4*>(As + (wm * 16 * NB + i * 16 + r16) * FLD + ks * 16 + grp * 4);
-        fb[i] = *reinterpret_cast<const float4*>(Bs + (wn * 16 * NB + i * 16 + r16) * FLD + ks * 16 + grp * 4);
-      }
+      for (int i = 0; i < MB; ++i)
+        fa[i] = *reinterpret_cast<const float4*>(As + (wm * 16 * MB + i * 16 + r16) * FLD + ks * 16 + grp * 4);
 #pragma unroll
       for (int i = 0; i < NB; ++i)
+        fb[i] = *reinterpret_cast<const float4*>(Bs + (wn * 16 * NB + i * 16 + r16) * FLD + ks * 16 + grp * 4);
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
           acc[i][j] = mfma4(fa[i].x, fb[j].x, acc[i][j]);
@@ -183,7 +183,7 @@ __global__ __launch_bounds__(256) void gemm_tn_f32(GemmArgsF g, Epi epi) {
     }
   }
   __syncthreads();
-  epi(acc, g, tm, m0 + wm * 16 * NB, n0 + wn * 16 * NB, lane, lds);
+  epi(acc, g, tm, m0 + wm * 16 * MB, n0 + wn * 16 * NB, lane, lds);
 }
 
 GemmArgsF make_args(const float* a, const float* b, int M, int N, int K) {
@@ -210,11 +210,11 @@ hipError_t launch_linear_f32(const float* x, const float* w, float* y, int M, in
   // below one 64 x 64 tile per CU the quarter tiles keep four times as many CUs busy
   if (tiles(M, 64) * tiles(N, 64) >= 256) {
     g.tiles_n = int(tiles(N, 64));
-    hipLaunchKernelGGL((gemm_tn_f32<2, EpiStoreF>), dim3(unsigned(tiles(M, 64) * g.tiles_n)),
+    hipLaunchKernelGGL((gemm_tn_f32<2, 2, EpiStoreF>), dim3(unsigned(tiles(M, 64) * g.tiles_n)),
                        dim3(256), 0, s, g, e);
   } else {
     g.tiles_n = int(tiles(N, 32));
-    hipLaunchKernelGGL((gemm_tn_f32<1, EpiStoreF>), dim3(unsigned(tiles(M, 32) * g.tiles_n)),
+    hipLaunchKernelGGL((gemm_tn_f32<1, 1, EpiStoreF>), dim3(unsigned(tiles(M, 32) * g.tiles_n)),
                        dim3(256), 0, s, g, e);
   }
   return hipGetLastError();
@@ -223,10 +223,18 @@ hipError_t launch_linear_f32(const float* x, const float* w, float* y, int M, in
 hipError_t launch_lmhead_f32(const LmHeadLaunch& a, hipStream_t s) {
   GemmArgsF g = make_args(static_cast<const float*>(a.w_lm), static_cast<const float*>(a.u), a.V,
                           a.N, a.D);
-  g.tiles_n = int(tiles(a.N, LMT));
   EpiLseF e{a.partial, a.target, a.ids};
-  hipLaunchKernelGGL((gemm_tn_f32<2, EpiLseF>), dim3(unsigned(tiles(a.V, LMT) * g.tiles_n)),
-                     dim3(256), 0, s, g, e);
+  // below one 64 x 64 tile per CU 32 entries a tile keep twice as many CUs busy, each with half
+  // the chain of MFMAs (the partials stay those of 64 vocabulary rows)
+  if (tiles(a.V, LMT) * tiles(a.N, 64) >= 256) {
+    g.tiles_n = int(tiles(a.N, 64));
+    hipLaunchKernelGGL((gemm_tn_f32<2, 2, EpiLseF>), dim3(unsigned(tiles(a.V, LMT) * g.tiles_n)),
+                       dim3(256), 0, s, g, e);
+  } else {
+    g.tiles_n = int(tiles(a.N, 32));
+    hipLaunchKernelGGL((gemm_tn_f32<2, 1, EpiLseF>), dim3(unsigned(tiles(a.V, LMT) * g.tiles_n)),
+                       dim3(256), 0, s, g, e);
+  }
   return hipGetLastError();
 }
 
