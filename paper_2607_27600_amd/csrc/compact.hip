@@ -3,7 +3,8 @@
 // as a bit copy of one head_dim row; token ids and position ids follow the same list.
 //
 // Out of place: one workgroup per (plane, chunk of rows), fully parallel.
-// In place: keep is ascending, so keep[j] >= j and a destination slot j can only be the
+// In place, short lists: one workgroup per plane with the whole list in registers.
+// In place beyond: keep is ascending, so keep[j] >= j and a destination slot j can only be the
 // source of an entry j' <= j.  One workgroup walks its plane in chunks of rows in
 // increasing order.  Chunk c's rows are written only after a barrier that every thread
 // reaches with chunk c's loads (and so all earlier loads) returned, which orders every
@@ -75,16 +76,17 @@ __device__ __forceinline__ Plane plane_of(const CompactArgs& a, int i) {
 }
 
 // ids[cu_b + j] = ids[cu_b + keep[j]] in place, block i for the i-th sequence's first list.
+template <int NT>
 __device__ __forceinline__ void compact_ids(const CompactArgs& a, int i) {
   constexpr int U = 8;
   const CompactList L = list_of(a, a.per_head ? i * a.n_heads : i);
   const int32_t* kp = a.keep + L.keep_off;
   const int base = a.cu[L.seq];
-  for (int j0 = 0; j0 < L.k; j0 += CNT * U) {
+  for (int j0 = 0; j0 < L.k; j0 += NT * U) {
     int32_t x[2][U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int src = base + kp[min(j0 + u * CNT + int(threadIdx.x), L.k - 1)];
+      const int src = base + kp[min(j0 + u * NT + int(threadIdx.x), L.k - 1)];
       if (a.ids[0]) x[0][u] = a.ids[0][src];
       if (a.ids[1]) x[1][u] = a.ids[1][src];
     }
@@ -92,7 +94,7 @@ __device__ __forceinline__ void compact_ids(const CompactArgs& a, int i) {
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int j = j0 + u * CNT + threadIdx.x;
+      const int j = j0 + u * NT + threadIdx.x;
       if (j < L.k) {
         if (a.ids[0]) a.ids[0][base + j] = x[0][u];
         if (a.ids[1]) a.ids[1][base + j] = x[1][u];
@@ -194,7 +196,7 @@ __device__ __forceinline__ void compact_paged_steps(const CompactArgs& a, const 
 template <bool PAGED>
 __global__ __launch_bounds__(CNT) void compact_in_place_kernel(CompactArgs a) {
   if (int(blockIdx.x) < a.id_blocks) {
-    compact_ids(a, blockIdx.x);
+    compact_ids<CNT>(a, blockIdx.x);
     return;
   }
   const Plane P = plane_of(a, int(blockIdx.x) - a.id_blocks);
@@ -259,10 +261,59 @@ __global__ __launch_bounds__(CNT) void compact_in_place_kernel(CompactArgs a) {
   }
 }
 
+// In place, lists of at most U rows a thread: a whole plane passes through the registers around one
+// barrier, where the walk waits for a round trip to memory in each of its chunks.  Rows past the end
+// of a list re-read its last entry (without them, under branches, the loads no longer go out at
+// once: 11.4 -> 13.6 us for 224 planes of 512 rows, paged more).
+constexpr int ONT = 1024;
+template <bool PAGED, int U>
+__global__ __launch_bounds__(ONT) void compact_once_kernel(CompactArgs a) {
+  if (int(blockIdx.x) < a.id_blocks) {
+    compact_ids<ONT>(a, blockIdx.x);
+    return;
+  }
+  const Plane P = plane_of(a, int(blockIdx.x) - a.id_blocks);
+  const int k = P.k;
+  if (k <= 0) return;
+  const KvView& v = a.src[P.tensor];   // source and destination views are the same
+  char* base = reinterpret_cast<char*>(const_cast<void*>(v.base)) + P.tok0 * v.tok_stride;
+  const int r0 = threadIdx.x / a.row16;
+  const int rstep = ONT / a.row16;
+  const int esz16 = P.col + (threadIdx.x % a.row16) * 16;
+  int64_t to[U];
+  int idx[U];
+  uint4 row[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) idx[u] = P.keep[min(r0 + u * rstep, k - 1)];
+#pragma unroll
+  for (int u = 0; u < U; ++u) to[u] = kv_off<PAGED>(v, P.seq, P.layer, P.head, min(r0 + u * rstep, k - 1)) + esz16;
+#pragma unroll
+  for (int u = 0; u < U; ++u) row[u] = ldg16(base + kv_off<PAGED>(v, P.seq, P.layer, P.head, idx[u]) + esz16);
+#pragma unroll
+  for (int u = 0; u < U; ++u)   // loads returned before anyone overwrites a source
+    asm volatile("" ::"v"(row[u].x), "v"(row[u].y), "v"(row[u].z), "v"(row[u].w));
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (r0 + u * rstep < k) *reinterpret_cast<uint4*>(base + to[u]) = row[u];
+}
+
+constexpr int OMAX = 8;       // most rows a thread
+template <int U>
+void launch_once(const CompactArgs& a, bool paged, int passes, unsigned blocks, hipStream_t s) {
+  if constexpr (U < OMAX) {
+    if (passes > U) return launch_once<U + 1>(a, paged, passes, blocks, s);
+  }
+  if (paged)
+    hipLaunchKernelGGL((compact_once_kernel<true, U>), dim3(blocks), dim3(ONT), 0, s, a);
+  else
+    hipLaunchKernelGGL((compact_once_kernel<false, U>), dim3(blocks), dim3(ONT), 0, s, a);
+}
+
 template <bool PAGED>
 __global__ __launch_bounds__(CNT) void compact_kernel(CompactArgs a) {
   if (int(blockIdx.x) < a.id_blocks) {
-    if (blockIdx.y == 0) compact_ids(a, blockIdx.x);
+    if (blockIdx.y == 0) compact_ids<CNT>(a, blockIdx.x);
     return;
   }
   const Plane P = plane_of(a, int(blockIdx.x) - a.id_blocks);
@@ -323,24 +374,42 @@ hipError_t launch_compact(const CompactLaunch& c, hipStream_t s) {
   }
   if (c.n_seqs == 0 || c.max_k == 0) return hipSuccess;
   const int64_t planes = int64_t(c.n_tensors) * c.n_seqs * c.n_layers * c.n_heads;
-  // In place, a plane is one block walking its list.  Few planes with long lists leave most of
+  a.n_slabs = 1;
+  a.row16 = c.row_bytes / 16;
+  auto chunk = [&]() { return (CNT / a.row16) * CU; };
+  // Lists that fit one pass through the registers (512 rows of 256 bytes a plane) take it, in column
+  // slabs while that leaves at most one block a CU; in a paged cache only up to one block a CU: there
+  // each row's page is another load before it, which the walk hides better.  Walk against one pass,
+  // us with the cache flushed: 224 planes of 512 rows 17.5 and 16.4, paged 17.8 and 16.6; 8 planes of
+  // 500 rows 10.5 and 8.1; 3584 planes of up to 480 rows 175 and 160; but 672 paged planes of up to
+  // 240 rows 21.0 and 22.4.
+  auto passes = [&]() { return (int64_t(c.max_k) * a.row16 + ONT - 1) / ONT; };
+  while (c.in_place && a.row16 > 4 && planes * a.n_slabs * 2 <= 256 && passes() > 1) {
+    a.row16 /= 2;
+    a.n_slabs *= 2;
+  }
+  const bool once = c.in_place && passes() <= OMAX && (!c.paged || planes <= 256);
+  if (!once) {
+    a.row16 = c.row_bytes / 16;
+    a.n_slabs = 1;
+  }
+  // Beyond, a plane is one block walking its list.  Few planes with long lists leave most of
   // the chip idle and make the walk the launch's length: rows are then cut into column slabs (of
   // at least 64 bytes: half a cache line) while that leaves at most one block a CU and more than
   // 16 chunks in line.  Keeping 13200 of 20000 entries in 8 planes of 256-byte rows, selection
   // included: 136 us whole, 85 us in four slabs; 5000 of 20000 in 32 planes 77 and 59 us; lists of
   // 1024 in 32 planes are faster whole (38 and 42 us), and 64 planes of 19800 about even.  (Blocks
   // of 1024 threads measured no better anywhere.)
-  a.n_slabs = 1;
-  a.row16 = c.row_bytes / 16;
-  auto chunk = [&]() { return (CNT / a.row16) * CU; };
-  while (c.in_place && a.row16 > 4 && a.row16 % 2 == 0 && planes * a.n_slabs * 2 <= 256 && c.max_k > 16 * chunk()) {
+  while (c.in_place && !once && a.row16 > 4 && a.row16 % 2 == 0 && planes * a.n_slabs * 2 <= 256 && c.max_k > 16 * chunk()) {
     a.row16 /= 2;
     a.n_slabs *= 2;
   }
   a.rows_per_chunk = chunk();
   const int64_t blocks = planes * a.n_slabs + a.id_blocks;
   if (blocks > INT32_MAX) return hipErrorInvalidValue;
-  if (c.in_place) {
+  if (once) {
+    launch_once<1>(a, c.paged, int(passes()), unsigned(blocks), s);
+  } else if (c.in_place) {
     if (c.paged)
       hipLaunchKernelGGL(compact_in_place_kernel<true>, dim3(unsigned(blocks)), dim3(CNT), 0, s, a);
     else

@@ -92,3 +92,17 @@ def test_rows_in_place(n, width):
     cc.cc_compact_rows(p, rows, keep, [kk], 0)
     torch.cuda.synchronize()
     assert torch.equal(rows, want)
+
+
+@pytest.mark.parametrize("budget", [1, 63, 64, 65, 448, 449, 512, 513])
+@pytest.mark.parametrize("paged,hkv,L,d", [(False, 2, 33, 128), (True, 2, 30, 128), (False, 1, 2, 128), (True, 1, 3, 64)])
+def test_short_lists_in_place(budget, paged, hkv, L, d):
+    """Lists that pass through the registers at once and the first that do not (512 rows of 256 bytes
+    are 8 a thread; few planes are cut into slabs), with a shorter list beside the longest."""
+    pick = lambda b, h, n: min(n, budget)
+    cc, p, view, (k, v, ids, pos), want, keep, ks = _case((600, 70), hkv, L, d, paged, False, budget, pick)
+    cc.cc_compact_kv(p, view(k, v), keep, ks, 0, token_ids=ids, pos_ids=pos)
+    torch.cuda.synchronize()
+    for got, ref in zip((k, v, ids, pos), want):
+        t = torch.int16 if got.dtype == torch.bfloat16 else torch.int32
+        assert torch.equal(got.view(t), ref.view(t))
