@@ -8,10 +8,10 @@
 // loaded while the current ones are multiplied.  A lane's 16-byte fragment is four
 // consecutive k, one for each of four MFMA steps (both operands agree on which).
 // Bound: launch and load latency for small problems, where 64 x 64 tiles leave most of the
-// chip idle and 32 x 32 ones are used instead; the fp32 MFMA rate beyond.  A 256 x 128 x 128
-// product went from 19 to 4 us, a 1024 x 256 x 128 LM head from 25 to 10 us (before: 64 x 64
-// tiles on the vector ALUs with element-wise loads); scoring 2048 entries of 16 heads of 128
-// on a 32000 x 1024 head from 11.4 to 1.67 ms.
+// chip idle and 32 x 32 or (LM head) 64 x 32 ones are used instead; the fp32 MFMA rate beyond.
+// Against 64 x 64 tiles on the vector ALUs with element-wise loads, a 256 x 128 x 128 product
+// went from 19 to 4 us, a 1024 x 256 x 128 LM head from 25 to 6.4 us (9.7 in 64 x 64 tiles);
+// scoring 2048 entries of 16 heads of 128 on a 32000 x 1024 head from 11.4 to 1.67 ms.
 #include "cc_internal.h"
 
 namespace cc {

@@ -66,7 +66,7 @@ def test_linear(M, N, K, off):
     assert np.all(np.abs(f64(y) - ref) <= bound)
 
 
-@pytest.mark.parametrize("N,D,V", [(1, 64, 1), (63, 33, 65), (64, 128, 64), (65, 100, 1000)])
+@pytest.mark.parametrize("N,D,V", [(1, 64, 1), (63, 33, 65), (64, 128, 64), (65, 100, 1000), (1030, 40, 1000)])
 def test_lmhead(N, D, V):
     from paper_2607_27600_amd import cc
     r = np.random.default_rng(7)
