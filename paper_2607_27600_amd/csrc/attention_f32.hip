@@ -2,11 +2,11 @@
 // every cached entry i attends only to later entries j > i of its own sequence.
 //
 // S^T = K Q^T and O^T = V^T P^T on the 16x16x4 fp32 MFMA (plain fp32 multiply-adds).  One
-// workgroup owns 32 rows, a row being one (position, query head of the GQA group) pair; its
-// four waves share those rows and take every fourth 16-key tile each, so a row's serial
-// chain is a quarter of its keys, and their (max, sum, output) triples are merged through
-// LDS.  A lane's column of the MFMA output is one row, so the online softmax needs two
-// shuffles per tile.  The k index of an MFMA is free to choose as long as both operands
+// workgroup owns 32 rows, a row being one (position, query head of the GQA group) pair; its W
+// waves share those rows and take every W-th 16-key tile each, so a row's serial chain is that
+// part of its keys, and their (max, sum, output) triples are merged through LDS.  W is 4, or 8 for
+// launches that leave CUs idle (launch_f32 has the rule).  A lane's column of the MFMA output is
+// one row, so the online softmax needs two shuffles per tile.  The k index of an MFMA is free to choose as long as both operands
 // agree, and is chosen so that every operand arrives by 16-byte loads straight from the
 // cache and P needs no data movement at all:
 //   S^T: lane group grp of four holds dims grp*d/4 .. +d/4-1 of its key row (step s takes
@@ -23,7 +23,6 @@ namespace {
 
 constexpr int F_ROWS = 32;   // rows per workgroup
 constexpr int F_BN = 16;     // keys per tile
-constexpr int F_WAVES = 4;
 
 template <class Items>
 struct AttnArgsF {
@@ -47,16 +46,16 @@ __device__ __forceinline__ bool non_finite(float x) {
   return (__float_as_uint(x) & 0x7f800000u) == 0x7f800000u;
 }
 
-template <int D, bool PAGED, class Items>
-__global__ __launch_bounds__(64 * F_WAVES) void attn_cc_f32(AttnArgsF<Items> a) {
+template <int D, bool PAGED, int W, class Items>
+__global__ __launch_bounds__(64 * W) void attn_cc_f32(AttnArgsF<Items> a) {
   constexpr int DL = D / 4;     // dims a lane holds of a key (or query) row
   constexpr int DB = D / 16;    // output blocks; dims a lane holds of a value row
   constexpr int OLD = D + 4;    // padded row of the merge buffer
-  __shared__ __attribute__((aligned(16))) float os[F_WAVES][F_ROWS][OLD];
-  __shared__ float ms[F_WAVES][F_ROWS], ls[F_WAVES][F_ROWS];
-  const AttnItem w = a.items.item(blockIdx.x);
-  const int b = w.seq, kvh = w.kvh, row0 = w.rb * F_ROWS;
-  const int seq0 = w.seq0, n = w.n;
+  __shared__ __attribute__((aligned(16))) float os[W][F_ROWS][OLD];
+  __shared__ float ms[W][F_ROWS], ls[W][F_ROWS];
+  const AttnItem it = a.items.item(blockIdx.x);
+  const int b = it.seq, kvh = it.kvh, row0 = it.rb * F_ROWS;
+  const int seq0 = it.seq0, n = it.n;
   const int g = a.g, nrows = n * g;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int grp = lane >> 4, r16 = lane & 15;
@@ -87,7 +86,7 @@ __global__ __launch_bounds__(64 * F_WAVES) void attn_cc_f32(AttnArgsF<Items> a) 
 #pragma unroll
   for (int db = 0; db < DB; ++db) acc[db][0] = acc[db][1] = f32x4{};
 
-  for (int t = t_begin + wave; t < t_end; t += F_WAVES) {
+  for (int t = t_begin + wave; t < t_end; t += W) {
     const int key0 = t * F_BN;
     // rows past the sequence end are clamped to its last key (their weights are 0)
     const float* kp = kb + kv_off<PAGED>(a.k, b, a.layer, kvh, min(key0 + r16, n - 1)) + grp * DL;
@@ -179,7 +178,7 @@ __global__ __launch_bounds__(64 * F_WAVES) void attn_cc_f32(AttnArgsF<Items> a) 
     }
   }
 
-  // merge the four waves: lane element i of block db is dim (4 grp + i) * DB + db
+  // merge the waves: lane element i of block db is dim (4 grp + i) * DB + db
 #pragma unroll
   for (int qb = 0; qb < 2; ++qb) {
     l[qb] += __shfl_xor(l[qb], 16);
@@ -197,15 +196,15 @@ __global__ __launch_bounds__(64 * F_WAVES) void attn_cc_f32(AttnArgsF<Items> a) 
             make_float4(acc[db][qb][i], acc[db + 1][qb][i], acc[db + 2][qb][i], acc[db + 3][qb][i]);
   }
   __syncthreads();
-  constexpr int TPR = 64 * F_WAVES / F_ROWS;   // threads per row
+  constexpr int TPR = 64 * W / F_ROWS;   // threads per row
   const int r = tid / TPR, row = row0 + r;
   if (row >= nrows) return;
-  float M = -INFINITY, L = 0.f, wgt[F_WAVES];
+  float M = -INFINITY, L = 0.f, wgt[W];
 #pragma unroll
-  for (int i = 0; i < F_WAVES; ++i) M = fmaxf(M, ms[i][r]);
+  for (int i = 0; i < W; ++i) M = fmaxf(M, ms[i][r]);
   const float ref = M == -INFINITY ? 0.f : M;
 #pragma unroll
-  for (int i = 0; i < F_WAVES; ++i) {
+  for (int i = 0; i < W; ++i) {
     wgt[i] = expf(ms[i][r] - ref);
     L += wgt[i] * ls[i][r];
   }
@@ -216,12 +215,12 @@ __global__ __launch_bounds__(64 * F_WAVES) void attn_cc_f32(AttnArgsF<Items> a) 
     const int e = c * TPR + tid % TPR;
     float x = 0.f;
 #pragma unroll
-    for (int i = 0; i < F_WAVES; ++i) x += wgt[i] * os[i][r][e];
+    for (int i = 0; i < W; ++i) x += wgt[i] * os[i][r][e];
     op[e] = x * inv;
   }
 }
 
-template <class Items>
+template <int D, int W, class Items>
 hipError_t launch_f32(const AttnLaunch& a, const Items& items, hipStream_t s) {
   AttnArgsF<Items> x;
   x.items = items;
@@ -234,19 +233,22 @@ hipError_t launch_f32(const AttnLaunch& a, const Items& items, hipStream_t s) {
   x.g = a.n_heads_q / a.n_heads_kv;
   x.scale = a.scale;
   x.inclusive = a.inclusive;
-  const dim3 grid(a.n_work), block(64 * F_WAVES);
-  if (a.head_dim == 64) {
-    if (a.paged)
-      hipLaunchKernelGGL((attn_cc_f32<64, true, Items>), grid, block, 0, s, x);
-    else
-      hipLaunchKernelGGL((attn_cc_f32<64, false, Items>), grid, block, 0, s, x);
-  } else {
-    if (a.paged)
-      hipLaunchKernelGGL((attn_cc_f32<128, true, Items>), grid, block, 0, s, x);
-    else
-      hipLaunchKernelGGL((attn_cc_f32<128, false, Items>), grid, block, 0, s, x);
-  }
+  const dim3 grid(a.n_work), block(64 * W);
+  if (a.paged)
+    hipLaunchKernelGGL((attn_cc_f32<D, true, W, Items>), grid, block, 0, s, x);
+  else
+    hipLaunchKernelGGL((attn_cc_f32<D, false, W, Items>), grid, block, 0, s, x);
   return hipGetLastError();
+}
+
+// Eight waves an item where the launch leaves CUs idle and an item has tiles to share.  (At head dim
+// 128 eight waves leave each too few registers.  Tables stand for more than ATTN_INLINE sequences:
+// many items.)
+template <class Items>
+hipError_t launch_f32(const AttnLaunch& a, const Items& items, hipStream_t s) {
+  if (a.head_dim != 64) return launch_f32<128, 4>(a, items, s);
+  const bool wide = !a.items.table && a.n_work <= 256 && a.items.seqs[0].n >= 8 * F_BN;
+  return wide ? launch_f32<64, 8>(a, items, s) : launch_f32<64, 4>(a, items, s);
 }
 
 }  // namespace

@@ -1,5 +1,5 @@
 """GPU parity of the fp32 kernels at the edges of their tiles: attention (32-row blocks, 16-key
-tiles dealt to four waves), the projection and the LM head (64 x 64 and 32 x 32 tiles, 32
+tiles dealt to four or eight waves), the projection and the LM head (64 x 64 to 32 x 32 tiles, 32
 columns of K a step, element-wise loads where K or a pointer rules 16-byte ones out)."""
 import numpy as np
 import pytest
@@ -17,6 +17,10 @@ pytestmark = pytest.mark.gpu
     ((1, 31, 65, 130), 7, 1, 128, True, "strict"),
     ((97, 64), 8, 2, 64, True, "inclusive"),
     ((300,), 2, 1, 128, False, "inclusive"),
+    ((127,), 4, 2, 64, False, "strict"),        # the longest item has 8 tiles: four waves
+    ((128, 0, 1), 4, 2, 64, True, "strict"),    # from here eight, up to 256 items
+    ((530, 129, 3), 7, 1, 64, False, "inclusive"),
+    ((600, 580), 7, 1, 64, True, "strict"),     # 259 items: four
 ])
 def test_attention(lens, hq, hkv, d, paged, diag):
     from tests.test_gpu_attention import _run
