@@ -69,15 +69,15 @@ __device__ __forceinline__ uint32_t order_key(float f) {
 // otherwise the one tile stays in registers.  Bound by vector ALU issue and LDS atomics:
 //  - Extremes of the finite scores, so that an infinite one (that of a sequence's last entry)
 //    does not squeeze all others into one bin.
-//  - bin = (f - fmin) * (NB - 2) / (fmax - fmin), clamped to 0 .. NB - 1: subtraction, product,
-//    clamp and truncation are monotone, so a higher bin never holds a lower score, whatever the
+//  - bin = (f - fmin) * (NB - 2) / (fmax - fmin) by one fused multiply-add, clamped to 0 .. NB - 1:
+//    multiply-add, clamp and truncation are monotone, so a higher bin never holds a lower score, whatever the
 //    rounding (a range that overflows or vanishes leaves one or two bins).  Digits of the float's
 //    bits in its place put scores between 8 and 16 nats, where most lie, into 8 bins: lanes of one
 //    instruction collide on them, and the threshold's bin holds thousands of scores.
-//    Selection calls back to back, float digits -> these bins: 4096 of 32768 scores in each of
-//    eight segments 25.7 -> 15.4 us, 514 of 768 scores 15.2 -> 8.3 us (four 8-bit digits before),
-//    16384 of 131072 scores 246 -> 51 us (likewise, 4-byte loads before).
-//  - NaN scores enter no bin: when the bins hold fewer than k scores, T is NaN.
+//    Selection calls back to back, digits -> bins: 4096 of 32768 scores in each of eight segments
+//    25.7 -> 12.9 us, 16384 of 131072 scores 246 -> 43 us (five passes of 4-byte loads before), 4096
+//    segments of 32768 scores 289 -> 232 us.
+//  - A NaN counts in bin 0, where its key (0) is below all others.
 //  - Up to CMAX scores of T's bin go to an LDS list (in any order).  Up to RANK of them are ranked
 //    by comparing each with all; more are searched by block-wide digits of their offset from the
 //    bin's smallest, and beyond CMAX that search runs over the tiles in place of the list.
@@ -91,6 +91,7 @@ __device__ __forceinline__ uint32_t order_key(float f) {
 constexpr int RNT = 1024;
 constexpr int RCW = 4;                 // scores per thread per chunk
 constexpr int CMAX = 4096;             // candidate list
+constexpr uint32_t FIN_SHIFT = 0x00800000u;   // bits + FIN_SHIFT: of non-negative scores +inf alone turns negative
 constexpr uint32_t RANK = 256;         // candidates ranked by comparison
 
 // The float of an order key.
@@ -121,17 +122,17 @@ constexpr auto fmin_bits = [](uint32_t a, uint32_t b) {
 constexpr auto fmax_bits = [](uint32_t a, uint32_t b) {
   return __float_as_uint(fmaxf(__uint_as_float(a), __uint_as_float(b)));
 };
+constexpr auto imax_bits = [](uint32_t a, uint32_t b) { return uint32_t(max(int32_t(a), int32_t(b))); };
 constexpr auto umin_bits = [](uint32_t a, uint32_t b) { return min(a, b); };
 constexpr auto umax_bits = [](uint32_t a, uint32_t b) { return max(a, b); };
 
 struct Pick {
-  uint32_t digit, rem, cnt;   // cnt == 0: fewer than rem keys are counted
+  uint32_t digit, rem, cnt;
 };
 
 // Run by one whole wave: in a histogram of 64 * BPL bins searched from the highest bin down,
-// the bin holding the rem-th largest counted key (rem >= 1), the rank left inside it and its
-// count; every lane receives the result.  When all bins hold fewer, rem is what is left after
-// them.  Level 1: lane l sums bins 64 BPL - BPL (l + 1) .. 64 BPL - 1 - BPL l and a wave scan
+// the bin holding the rem-th largest counted key (1 <= rem <= total), the rank left inside it and
+// its count; every lane receives the result.  Level 1: lane l sums bins 64 BPL - BPL (l + 1) .. 64 BPL - 1 - BPL l and a wave scan
 // finds the lane whose range holds the rank; level 2: lane j < BPL reads that range's j-th
 // highest bin and a second scan finds the bin.
 template <int BPL>
@@ -147,8 +148,7 @@ __device__ __forceinline__ Pick pick_bucket(const uint32_t* h, uint32_t rem, int
   }
   const uint32_t incl = wave_incl_scan(sum, lane);
   const uint64_t over = __ballot(incl >= rem);
-  if (over == 0) return {0u, rem - uint32_t(__builtin_amdgcn_readlane(int(incl), 63)), 0u};
-  const int owner = int(__builtin_ctzll(over));
+  const int owner = over ? int(__builtin_ctzll(over)) : 63;   // rem <= total: some lane does
   const uint32_t before = uint32_t(__builtin_amdgcn_readlane(int(incl - sum), owner));
   const int top = NB - BPL * owner - 1;              // the owner's highest bin
   const uint32_t c = lane < BPL ? h[top - lane] : 0u;
@@ -168,7 +168,7 @@ struct KeepLds {
   __attribute__((aligned(16))) uint32_t hist[NB];
   __attribute__((aligned(16))) uint32_t cand[NC];
   __attribute__((aligned(16))) uint32_t wtot[4][NW][NQ];
-  uint32_t red[4][NW];
+  uint32_t red[7][NW];
   uint32_t sh_key, sh_rem, sh_cnt, sh_ncand;
 };
 
@@ -298,58 +298,101 @@ __global__ __launch_bounds__(NT, 1) void select_keep_kernel(const float* __restr
       }
     };
     if constexpr (!STREAM) load(0);
-
-    // the finite scores' extremes
-    float mn = INFINITY, mx = -INFINITY;
-    tiles([&](uint32_t) {
+    // fn(slot) for the scores of the tile at t0, without what lies past the end
+    auto each_score = [&](uint32_t t0, auto&& fn) {
+      uint32_t t4 = t0 + RCW * tid;
+      asm volatile("" : "+v"(t4));
 #pragma unroll
-      for (int j = 0; j < SPT; ++j) {
-        const bool fin = fabsf(f[j]) < INFINITY;
-        mn = fminf(mn, fin ? f[j] : mn);
-        mx = fmaxf(mx, fin ? f[j] : mx);
+      for (int c = 0; c < CH; ++c) {
+        if (t0 + (c + 1) * CHUNK <= uint32_t(n)) {   // uniform: the chunk is whole
+#pragma unroll
+          for (int u = 0; u < RCW; ++u) fn(RCW * c + u);
+        } else if (t0 + c * CHUNK < uint32_t(n)) {
+#pragma unroll
+          for (int u = 0; u < RCW; ++u)
+            if (c * CHUNK + t4 + u < uint32_t(n)) fn(RCW * c + u);
+        }
       }
+    };
+
+    // The finite scores' extremes.  First taken for scores of language models, none negative and none
+    // NaN: their bits compare as integers, and adding FIN_SHIFT takes +inf alone below all others
+    // (2.5 instructions a score).  Bits above those of +inf (a sign, a NaN) or no finite score:
+    // taken again, score by score.
+    uint32_t lo_b = 0xffffffffu, hi_b = 0u;
+    int32_t fin_b = int32_t(0x80000000u);
+    tiles([&](uint32_t t0) {
+      each_score(t0, [&](int j) {
+        const uint32_t u = __float_as_uint(f[j]);
+        lo_b = min(lo_b, u);
+        hi_b = max(hi_b, u);
+        fin_b = max(fin_b, int32_t(u + FIN_SHIFT));
+      });
     });
     __syncthreads();   // the segment before is done with the LDS
     {
-      const uint32_t r0 = wave_reduce(__float_as_uint(mn), __float_as_uint(INFINITY), fmin_bits);
-      const uint32_t r1 = wave_reduce(__float_as_uint(mx), __float_as_uint(-INFINITY), fmax_bits);
+      const uint32_t r0 = wave_reduce(lo_b, 0xffffffffu, umin_bits);
+      const uint32_t r1 = wave_reduce(hi_b, 0u, umax_bits);
+      const uint32_t r2 = wave_reduce(uint32_t(fin_b), 0x80000000u, imax_bits);
       if (lane == 0) {
         L.red[0][wave] = r0;
         L.red[1][wave] = r1;
+        L.red[2][wave] = r2;
       }
     }
     for (int i = tid; i < NB; i += NT) L.hist[i] = 0u;
     if (tid == 0) L.sh_ncand = 0u;
     __syncthreads();
-    mn = __uint_as_float(row0_reduce(lane < NW ? L.red[0][lane] : __float_as_uint(INFINITY),
-                                     __float_as_uint(INFINITY), fmin_bits));
-    mx = __uint_as_float(row0_reduce(lane < NW ? L.red[1][lane] : __float_as_uint(-INFINITY),
-                                     __float_as_uint(-INFINITY), fmax_bits));
-    const float inv = float(NB - 2) / (mx - mn);
-    // a product of 0 and infinity is NaN, which the clamp takes to 0
-    auto bin_of = [&](float x) { return uint32_t(fminf(fmaxf((x - mn) * inv, 0.f), float(NB - 1))); };
-
-    if (mn != mx) {
+    lo_b = row0_reduce(lane < NW ? L.red[0][lane] : 0xffffffffu, 0xffffffffu, umin_bits);
+    hi_b = row0_reduce(lane < NW ? L.red[1][lane] : 0u, 0u, umax_bits);
+    fin_b = int32_t(row0_reduce(lane < NW ? L.red[2][lane] : 0x80000000u, 0x80000000u, imax_bits));
+    const bool clean = hi_b <= 0x7f800000u && fin_b >= int32_t(FIN_SHIFT);   // uniform
+    float mn = __uint_as_float(lo_b), mx = __uint_as_float(uint32_t(fin_b) - FIN_SHIFT);
+    if (!clean) {
+      mn = INFINITY;
+      mx = -INFINITY;
       tiles([&](uint32_t) {
 #pragma unroll
-        for (int j = 0; j < SPT; ++j)
-          if (f[j] == f[j]) atomicAdd(&L.hist[bin_of(f[j])], 1u);
+        for (int j = 0; j < SPT; ++j) {
+          const bool fin = fabsf(f[j]) < INFINITY;
+          mn = fminf(mn, fin ? f[j] : mn);
+          mx = fmaxf(mx, fin ? f[j] : mx);
+        }
+      });
+      const uint32_t r0 = wave_reduce(__float_as_uint(mn), __float_as_uint(INFINITY), fmin_bits);
+      const uint32_t r1 = wave_reduce(__float_as_uint(mx), __float_as_uint(-INFINITY), fmax_bits);
+      if (lane == 0) {
+        L.red[3][wave] = r0;
+        L.red[4][wave] = r1;
+      }
+      __syncthreads();
+      mn = __uint_as_float(row0_reduce(lane < NW ? L.red[3][lane] : __float_as_uint(INFINITY),
+                                       __float_as_uint(INFINITY), fmin_bits));
+      mx = __uint_as_float(row0_reduce(lane < NW ? L.red[4][lane] : __float_as_uint(-INFINITY),
+                                       __float_as_uint(-INFINITY), fmax_bits));
+    }
+    const float inv = mn < mx ? float(NB - 2) / (mx - mn) : 1.f;
+    const float at0 = -mn * inv;
+    // NaN goes to bin 0: that of a score, and that of 0 times infinity or infinity less itself, which
+    // then takes every lower score with it
+    auto bin_of = [&](float x) { return uint32_t(fminf(fmaxf(fmaf(x, inv, at0), 0.f), float(NB - 1))); };
+
+    if (mn != mx) {
+      tiles([&](uint32_t t0) {
+        each_score(t0, [&](int j) { atomicAdd(&L.hist[bin_of(f[j])], 1u); });
       });
     } else {
       // Equal finite scores share bin 0, where every lane's atomic would wait for all others: a wave
       // adds them up first (eight segments of 32768 equal scores: 45 us by atomics alone, 20 us).
       uint32_t zeros = 0u;
-      tiles([&](uint32_t) {
-#pragma unroll
-        for (int j = 0; j < SPT; ++j) {
-          if (f[j] == f[j]) {
-            const uint32_t b = bin_of(f[j]);
-            if (b == 0u)
-              ++zeros;
-            else
-              atomicAdd(&L.hist[b], 1u);
-          }
-        }
+      tiles([&](uint32_t t0) {
+        each_score(t0, [&](int j) {
+          const uint32_t b = bin_of(f[j]);
+          if (b == 0u)
+            ++zeros;
+          else
+            atomicAdd(&L.hist[b], 1u);
+        });
       });
       zeros = wave_reduce(zeros, 0u, [](uint32_t a, uint32_t b) { return a + b; });
       if (lane == 0) atomicAdd(&L.hist[0], zeros);
@@ -367,8 +410,8 @@ __global__ __launch_bounds__(NT, 1) void select_keep_kernel(const float* __restr
     const uint32_t bin = L.sh_key;
     uint32_t rem = L.sh_rem, cnt = L.sh_cnt;   // T is the rem-th largest of the bin's cnt scores
     uint32_t T = 0u;                           // its order key
-    if (cnt != 0u) {
-      auto here = [&](float x) { return x == x && bin_of(x) == bin; };
+    {
+      auto here = [&](int j) { return bin_of(f[j]) == bin; };
       // T by block-wide digits of key - kmin (scores that are all equal leave no digit); each(visit)
       // visits this thread's keys of the bin
       auto search = [&](auto&& each) {
@@ -380,12 +423,12 @@ __global__ __launch_bounds__(NT, 1) void select_keep_kernel(const float* __restr
         const uint32_t r0 = wave_reduce(kmin, 0xffffffffu, umin_bits);
         const uint32_t r1 = wave_reduce(kmax, 0u, umax_bits);
         if (lane == 0) {
-          L.red[2][wave] = r0;
-          L.red[3][wave] = r1;
+            L.red[5][wave] = r0;
+          L.red[6][wave] = r1;
         }
         __syncthreads();
-        kmin = row0_reduce(lane < NW ? L.red[2][lane] : 0xffffffffu, 0xffffffffu, umin_bits);
-        kmax = row0_reduce(lane < NW ? L.red[3][lane] : 0u, 0u, umax_bits);
+        kmin = row0_reduce(lane < NW ? L.red[5][lane] : 0xffffffffu, 0xffffffffu, umin_bits);
+        kmax = row0_reduce(lane < NW ? L.red[6][lane] : 0u, 0u, umax_bits);
         int hi = kmax > kmin ? 32 - __clz(kmax - kmin) : 0;   // offsets < 2^hi
         uint32_t prefix = 0u;                                 // offset >> hi of those in the running
         while (hi > 0) {
@@ -416,17 +459,16 @@ __global__ __launch_bounds__(NT, 1) void select_keep_kernel(const float* __restr
         T = kmin + prefix;
       };
       if (cnt <= uint32_t(NC)) {
-        tiles([&](uint32_t) {
-#pragma unroll
-          for (int j = 0; j < SPT; ++j) {
+        tiles([&](uint32_t t0) {
+          each_score(t0, [&](int j) {
             // a score enters the list where it finds it (the search needs no order); the
             // increments of one instruction are combined by a single lane
-            if (here(f[j])) {
+            if (here(j)) {
               const uint32_t pos = atomicAdd(&L.sh_ncand, 1u);
               if (pos < uint32_t(NC)) L.cand[pos] = order_key(f[j]);
             }
             __builtin_amdgcn_sched_barrier(0);   // one score at a time: no 32 live masks
-          }
+          });
         });
         __syncthreads();
         if (cnt <= RANK) {
@@ -460,12 +502,11 @@ __global__ __launch_bounds__(NT, 1) void select_keep_kernel(const float* __restr
         }
       } else if constexpr (NC < TILE || STREAM) {
         search([&](auto&& visit) {
-          tiles([&](uint32_t) {
-#pragma unroll
-            for (int j = 0; j < SPT; ++j) {
-              if (here(f[j])) visit(order_key(f[j]));
-              __builtin_amdgcn_sched_barrier(0);   // one score at a time: no 32 live masks
-            }
+          tiles([&](uint32_t t0) {
+            each_score(t0, [&](int j) {
+              if (here(j)) visit(order_key(f[j]));
+              __builtin_amdgcn_sched_barrier(0);
+            });
           });
         });
       }
@@ -484,8 +525,12 @@ __global__ __launch_bounds__(NT, 1) void select_keep_kernel(const float* __restr
     tiles([&](uint32_t t0) {
       uint32_t take = 0u, own[NQ], base[CH];
       if (all_ties) {
+        // counted per chunk (no mask: the stores compare again)
+        uint32_t n_c[2 * NQ] = {};
 #pragma unroll
-        for (int j = SPT - 1; j >= 0; --j) take = (take << 1) | uint32_t(f[j] >= tf);
+        for (int j = 0; j < SPT; ++j) n_c[j / RCW] += uint32_t(f[j] >= tf);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) own[q] = n_c[2 * q] | (n_c[2 * q + 1] << 16);
       } else {
         // ties ranked in index order; the first rem are kept
         uint32_t eq = 0u;
@@ -501,29 +546,35 @@ __global__ __launch_bounds__(NT, 1) void select_keep_kernel(const float* __restr
           const uint32_t below = uint32_t(__popc(eq & (((1u << (j & 3)) - 1u) << (j & ~3))));
           take |= uint32_t(((eq >> j) & 1u) && base[j >> 2] + below < rem) << j;
         }
+        chunk_counts(take, own);
       }
-      chunk_counts(take, own);
       chunk_offsets<NW, CH, NQ>(own, base, kept, L.wtot[par], lane, wave);
       par ^= 1;
       uint32_t t4 = t0 + RCW * tid;
       asm volatile("" : "+v"(t4));
       // kept scores of chunk c at ranks base[c], base[c] + 1, ...
+      auto emit = [&](auto&& is_kept) {
 #pragma unroll
-      for (int c = 0; c < CH; ++c) {
-        uint32_t r = base[c];
+        for (int c = 0; c < CH; ++c) {
+          uint32_t r = base[c];
 #pragma unroll
-        for (int u = 0; u < RCW; ++u) {
-          if ((take >> (RCW * c + u)) & 1u) {
-            const uint32_t i = c * CHUNK + t4 + u;
-            if constexpr (STREAM) {   // a budget may exceed a descriptor's 4 GB
-              if (r < uint32_t(k)) out[r] = int32_t(i);
-            } else {
-              __builtin_amdgcn_raw_buffer_store_b32(i, rs, int(4u * r), 0, 0);
+          for (int u = 0; u < RCW; ++u) {
+            if (is_kept(RCW * c + u)) {
+              const uint32_t i = c * CHUNK + t4 + u;
+              if constexpr (STREAM) {   // a budget may exceed a descriptor's 4 GB
+                if (r < uint32_t(k)) out[r] = int32_t(i);
+              } else {
+                __builtin_amdgcn_raw_buffer_store_b32(i, rs, int(4u * r), 0, 0);
+              }
+              ++r;
             }
-            ++r;
           }
         }
-      }
+      };
+      if (all_ties)
+        emit([&](int j) { return f[j] >= tf; });
+      else
+        emit([&](int j) { return ((take >> j) & 1u) != 0u; });
     });
   }
 }
@@ -564,7 +615,7 @@ hipError_t launch_select(const float* scores, const SelSeg* segs_h, const SelSeg
     inl.k = segs_h[0].k;
   }
   // The smallest kernel that holds the longest segment in registers: each further chunk costs a
-  // short segment instructions and barriers (8000 scores: 8.7 us in two chunks, 12.5 us in eight).
+  // short segment instructions (8192 scores in two chunks take 3 us less than 9001 in eight).
   if (max_len <= 256 * RCW)
     launch_keep<256, 1, false>(scores, segs_d, inl, n_segs, n_segs, keep, s);
   else if (max_len <= RNT * RCW)
