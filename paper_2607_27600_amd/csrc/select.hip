@@ -69,18 +69,20 @@ __device__ __forceinline__ uint32_t order_key(float f) {
 // otherwise the one tile stays in registers.  Bound by vector ALU issue and LDS atomics:
 //  - Extremes of the finite scores, so that an infinite one (that of a sequence's last entry)
 //    does not squeeze all others into one bin.
-//  - bin = (f - fmin) * (NB - 2) / (fmax - fmin) by one fused multiply-add, clamped to 0 .. NB - 1:
-//    multiply-add, clamp and truncation are monotone, so a higher bin never holds a lower score, whatever the
-//    rounding (a range that overflows or vanishes leaves one or two bins).  Digits of the float's
-//    bits in its place put scores between 8 and 16 nats, where most lie, into 8 bins: lanes of one
-//    instruction collide on them, and the threshold's bin holds thousands of scores.
-//    Selection calls back to back, digits -> bins: 4096 of 32768 scores in each of eight segments
-//    25.7 -> 12.9 us, 16384 of 131072 scores 246 -> 43 us (five passes of 4-byte loads before), 4096
-//    segments of 32768 scores 289 -> 232 us.
+//  - bin = (f - min) * (NB - 2) / (max - min) by one fused multiply-add that also makes it a whole
+//    number, clamped to 0 .. NB - 1: both are monotone, so a higher bin never holds a lower score,
+//    whatever the rounding (a range that overflows or vanishes leaves one or two bins).  Digits of
+//    the float's bits in its place put scores between 8 and 16 nats, where most lie, into 8 bins:
+//    lanes of one instruction collide on them, and the threshold's bin holds thousands of scores.
+//    4096 of 32768 scores in each of eight segments, digits and bins: 25.7 and 11.8 us; 16384 of
+//    131072 scores 244 and 38 us (five passes of 4-byte loads before); 8192 of 32768 scores in each
+//    of 4096 segments, caches flushed: 293 and 212 us for scores around 9 nats, 227 and 221 us for
+//    exponential ones, which digits spread well.
 //  - A NaN counts in bin 0, where its key (0) is below all others.
 //  - Up to CMAX scores of T's bin go to an LDS list (in any order).  Up to RANK of them are ranked
-//    by comparing each with all; more are searched by block-wide digits of their offset from the
-//    bin's smallest, and beyond CMAX that search runs over the tiles in place of the list.
+//    by comparing each with all, a wave a score (a thread a score: 2.0 us a segment against 0.7 at 41
+//    scores); more are searched by block-wide digits of their offset from the bin's smallest, and
+//    beyond CMAX that search runs over the tiles in place of the list.
 //  - Bucket searches are two-level wave scans: lane sums over the lanes' bin ranges, then
 //    the bins of the lane that holds the rank.
 //  - Emission: a thread's flagged scores per chunk are counted, and one batched scan over
@@ -92,7 +94,9 @@ constexpr int RNT = 1024;
 constexpr int RCW = 4;                 // scores per thread per chunk
 constexpr int CMAX = 4096;             // candidate list
 constexpr uint32_t FIN_SHIFT = 0x00800000u;   // bits + FIN_SHIFT: of non-negative scores +inf alone turns negative
-constexpr uint32_t RANK = 256;         // candidates ranked by comparison
+constexpr uint32_t RANK = 256;         // candidates ranked by comparison (a multiple of 64)
+constexpr float ONE = 8388608.f;       // 2^23: floats from here on to 2^24 are whole numbers
+constexpr uint32_t ONE_B = 0x4b000000u;
 
 // The float of an order key.
 __device__ __forceinline__ float key_float(uint32_t k) {
@@ -372,14 +376,16 @@ __global__ __launch_bounds__(NT, 1) void select_keep_kernel(const float* __restr
                                        __float_as_uint(-INFINITY), fmax_bits));
     }
     const float inv = mn < mx ? float(NB - 2) / (mx - mn) : 1.f;
-    const float at0 = -mn * inv;
-    // NaN goes to bin 0: that of a score, and that of 0 times infinity or infinity less itself, which
-    // then takes every lower score with it
-    auto bin_of = [&](float x) { return uint32_t(fminf(fmaxf(fmaf(x, inv, at0), 0.f), float(NB - 1))); };
+    const float at = fmaf(-mn, inv, ONE);
+    // Bits of ONE + the bin: the sum's unit is 1.  NaN goes to bin 0: that of a score, and that of
+    // 0 times infinity or infinity less itself, which then takes every lower score with it.
+    auto bin_of = [&](float x) {
+      return __float_as_uint(__builtin_amdgcn_fmed3f(fmaf(x, inv, at), ONE, ONE + float(NB - 1)));
+    };
 
     if (mn != mx) {
       tiles([&](uint32_t t0) {
-        each_score(t0, [&](int j) { atomicAdd(&L.hist[bin_of(f[j])], 1u); });
+        each_score(t0, [&](int j) { atomicAdd(&L.hist[bin_of(f[j]) - ONE_B], 1u); });
       });
     } else {
       // Equal finite scores share bin 0, where every lane's atomic would wait for all others: a wave
@@ -388,10 +394,10 @@ __global__ __launch_bounds__(NT, 1) void select_keep_kernel(const float* __restr
       tiles([&](uint32_t t0) {
         each_score(t0, [&](int j) {
           const uint32_t b = bin_of(f[j]);
-          if (b == 0u)
+          if (b == ONE_B)
             ++zeros;
           else
-            atomicAdd(&L.hist[b], 1u);
+            atomicAdd(&L.hist[b - ONE_B], 1u);
         });
       });
       zeros = wave_reduce(zeros, 0u, [](uint32_t a, uint32_t b) { return a + b; });
@@ -407,7 +413,7 @@ __global__ __launch_bounds__(NT, 1) void select_keep_kernel(const float* __restr
       }
     }
     __syncthreads();
-    const uint32_t bin = L.sh_key;
+    const uint32_t bin = ONE_B + L.sh_key;
     uint32_t rem = L.sh_rem, cnt = L.sh_cnt;   // T is the rem-th largest of the bin's cnt scores
     uint32_t T = 0u;                           // its order key
     {
@@ -423,7 +429,7 @@ __global__ __launch_bounds__(NT, 1) void select_keep_kernel(const float* __restr
         const uint32_t r0 = wave_reduce(kmin, 0xffffffffu, umin_bits);
         const uint32_t r1 = wave_reduce(kmax, 0u, umax_bits);
         if (lane == 0) {
-            L.red[5][wave] = r0;
+          L.red[5][wave] = r0;
           L.red[6][wave] = r1;
         }
         __syncthreads();
@@ -460,31 +466,49 @@ __global__ __launch_bounds__(NT, 1) void select_keep_kernel(const float* __restr
       };
       if (cnt <= uint32_t(NC)) {
         tiles([&](uint32_t t0) {
-          each_score(t0, [&](int j) {
-            // a score enters the list where it finds it (the search needs no order); the
-            // increments of one instruction are combined by a single lane
-            if (here(j)) {
-              const uint32_t pos = atomicAdd(&L.sh_ncand, 1u);
-              if (pos < uint32_t(NC)) L.cand[pos] = order_key(f[j]);
+          uint32_t t4 = t0 + RCW * tid;
+          asm volatile("" : "+v"(t4));
+#pragma unroll
+          for (int c = 0; c < CH; ++c) {
+            bool h[RCW], any = false;
+#pragma unroll
+            for (int u = 0; u < RCW; ++u) {
+              h[u] = here(RCW * c + u);
+              any |= h[u];
             }
-            __builtin_amdgcn_sched_barrier(0);   // one score at a time: no 32 live masks
-          });
+            if (__any(any)) {
+              // a score enters the list where it finds it (the search needs no order); the
+              // increments of one instruction are combined by a single lane
+#pragma unroll
+              for (int u = 0; u < RCW; ++u)
+                if (h[u] && c * CHUNK + t4 + u < uint32_t(n)) {
+                  const uint32_t pos = atomicAdd(&L.sh_ncand, 1u);
+                  if (pos < uint32_t(NC)) L.cand[pos] = order_key(f[RCW * c + u]);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);   // one chunk at a time: no 32 live masks
+          }
         });
         __syncthreads();
         if (cnt <= RANK) {
-          if (uint32_t(tid) < cnt) {
-            const uint32_t mine = L.cand[tid];
-            uint32_t above = 0u, same = 0u;
-            for (uint32_t i = 0; i < cnt; i += 4) {
-              const uint4 v = *reinterpret_cast<const uint4*>(&L.cand[i]);
-              const uint32_t x[4] = {v.x, v.y, v.z, v.w};
+          // one candidate a wave at a time: its rank is the count of lanes whose candidates compare so
+          uint32_t x[RANK / 64];
+          uint64_t has[RANK / 64];
 #pragma unroll
-              for (uint32_t u = 0; u < 4; ++u) {
-                above += uint32_t(i + u < cnt && x[u] > mine);
-                same += uint32_t(i + u < cnt && x[u] == mine);
-              }
+          for (int q = 0; q < int(RANK / 64); ++q) {
+            x[q] = L.cand[64 * q + lane];
+            has[q] = __ballot(64 * q + lane < int(cnt));
+          }
+          for (uint32_t c = wave; c < cnt; c += NW) {
+            const uint32_t mine = uint32_t(__builtin_amdgcn_readfirstlane(int(L.cand[c])));
+            uint32_t above = 0u, same = 0u;
+#pragma unroll
+            for (int q = 0; q < int(RANK / 64); ++q) {
+              if (64u * q >= cnt) break;
+              above += uint32_t(__popcll(__ballot(x[q] > mine) & has[q]));
+              same += uint32_t(__popcll(__ballot(x[q] == mine) & has[q]));
             }
-            if (above < rem && rem <= above + same) {   // one value; its holders write the same
+            if (lane == 0 && above < rem && rem <= above + same) {   // one value; its holders write the same
               L.sh_key = mine;
               L.sh_rem = rem - above;
               L.sh_cnt = same;
