@@ -11,7 +11,7 @@
 // everything behind the histogram compares exactly: the result is exact.
 //
 // Segments of up to 32768 scores are read once, into registers, by one of four sizes of the
-// kernel; longer ones are read again by each of the four passes.
+// kernel; longer ones are read again by each pass.
 #include <algorithm>
 
 #include "cc_internal.h"
@@ -74,10 +74,16 @@ __device__ __forceinline__ uint32_t order_key(float f) {
 //    whatever the rounding (a range that overflows or vanishes leaves one or two bins).  Digits of
 //    the float's bits in its place put scores between 8 and 16 nats, where most lie, into 8 bins:
 //    lanes of one instruction collide on them, and the threshold's bin holds thousands of scores.
-//    4096 of 32768 scores in each of eight segments, digits and bins: 25.7 and 11.8 us; 16384 of
+//    4096 of 32768 scores in each of eight segments, digits and bins: 25.7 and 12.0 us; 16384 of
 //    131072 scores 244 and 38 us (five passes of 4-byte loads before); 8192 of 32768 scores in each
-//    of 4096 segments, caches flushed: 293 and 212 us for scores around 9 nats, 227 and 221 us for
+//    of 4096 segments, caches flushed: 293 and 221 us for scores around 9 nats, 227 and 228 us for
 //    exponential ones, which digits spread well.
+//  - A far score (one entry pinned at 1e9) widens the range until all others share a bin.  Such a range
+//    is cut beforehand where a few scores cause it, and the bins are made anew over the threshold's
+//    bin where it holds more than the list does (half the entries masked with -1e30; two rounds
+//    of that, then digits).  Bins at the ends of the range that many scores share are counted in
+//    registers.  The eight segments and the 4096, digits, bins over the whole range, and now: one at 1e9
+//    25.8 and 291, 54 and 887, 12.9 and 237 us; half at -1e30 25.7 and 426, 42 and 701, 19.9 and 345.
 //  - A NaN counts in bin 0, where its key (0) is below all others.
 //  - Up to CMAX scores of T's bin go to an LDS list (in any order).  Up to RANK of them are ranked
 //    by comparing each with all, a wave a score (a thread a score: 2.0 us a segment against 0.7 at 41
@@ -129,6 +135,19 @@ constexpr auto fmax_bits = [](uint32_t a, uint32_t b) {
 constexpr auto imax_bits = [](uint32_t a, uint32_t b) { return uint32_t(max(int32_t(a), int32_t(b))); };
 constexpr auto umin_bits = [](uint32_t a, uint32_t b) { return min(a, b); };
 constexpr auto umax_bits = [](uint32_t a, uint32_t b) { return max(a, b); };
+constexpr auto add_bits = [](uint32_t a, uint32_t b) { return a + b; };
+
+// Of numbers (fminf and fmaxf would quiet each operand first: as many instructions again).
+__device__ __forceinline__ float min3(float a, float b, float c) {
+  float d;
+  asm("v_min3_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+  return d;
+}
+__device__ __forceinline__ float max3(float a, float b, float c) {
+  float d;
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+  return d;
+}
 
 struct Pick {
   uint32_t digit, rem, cnt;
@@ -347,76 +366,144 @@ __global__ __launch_bounds__(NT, 1) void select_keep_kernel(const float* __restr
     for (int i = tid; i < NB; i += NT) L.hist[i] = 0u;
     if (tid == 0) L.sh_ncand = 0u;
     __syncthreads();
-    lo_b = row0_reduce(lane < NW ? L.red[0][lane] : 0xffffffffu, 0xffffffffu, umin_bits);
+    const uint32_t lo_w = lane < NW ? L.red[0][lane] : 0xffffffffu;
+    const int32_t fin_w = lane < NW ? int32_t(L.red[2][lane]) : int32_t(0x80000000u);
+    lo_b = row0_reduce(lo_w, 0xffffffffu, umin_bits);
     hi_b = row0_reduce(lane < NW ? L.red[1][lane] : 0u, 0u, umax_bits);
-    fin_b = int32_t(row0_reduce(lane < NW ? L.red[2][lane] : 0x80000000u, 0x80000000u, imax_bits));
-    const bool clean = hi_b <= 0x7f800000u && fin_b >= int32_t(FIN_SHIFT);   // uniform
-    float mn = __uint_as_float(lo_b), mx = __uint_as_float(uint32_t(fin_b) - FIN_SHIFT);
-    if (!clean) {
-      mn = INFINITY;
-      mx = -INFINITY;
-      tiles([&](uint32_t) {
-#pragma unroll
-        for (int j = 0; j < SPT; ++j) {
-          const bool fin = fabsf(f[j]) < INFINITY;
-          mn = fminf(mn, fin ? f[j] : mn);
-          mx = fmaxf(mx, fin ? f[j] : mx);
-        }
-      });
-      const uint32_t r0 = wave_reduce(__float_as_uint(mn), __float_as_uint(INFINITY), fmin_bits);
-      const uint32_t r1 = wave_reduce(__float_as_uint(mx), __float_as_uint(-INFINITY), fmax_bits);
-      if (lane == 0) {
-        L.red[3][wave] = r0;
-        L.red[4][wave] = r1;
-      }
-      __syncthreads();
-      mn = __uint_as_float(row0_reduce(lane < NW ? L.red[3][lane] : __float_as_uint(INFINITY),
-                                       __float_as_uint(INFINITY), fmin_bits));
-      mx = __uint_as_float(row0_reduce(lane < NW ? L.red[4][lane] : __float_as_uint(-INFINITY),
-                                       __float_as_uint(-INFINITY), fmax_bits));
+    fin_b = int32_t(row0_reduce(uint32_t(fin_w), 0x80000000u, imax_bits));
+    if (lo_b == hi_b) {   // one value (or NaN): the first k
+      for (int i = tid; i < k; i += NT) out[i] = i;
+      continue;
     }
-    const float inv = mn < mx ? float(NB - 2) / (mx - mn) : 1.f;
-    const float at = fmaf(-mn, inv, ONE);
-    // Bits of ONE + the bin: the sum's unit is 1.  NaN goes to bin 0: that of a score, and that of
-    // 0 times infinity or infinity less itself, which then takes every lower score with it.
-    auto bin_of = [&](float x) {
-      return __float_as_uint(__builtin_amdgcn_fmed3f(fmaf(x, inv, at), ONE, ONE + float(NB - 1)));
-    };
-
-    if (mn != mx) {
-      tiles([&](uint32_t t0) {
-        each_score(t0, [&](int j) { atomicAdd(&L.hist[bin_of(f[j]) - ONE_B], 1u); });
-      });
-    } else {
-      // Equal finite scores share bin 0, where every lane's atomic would wait for all others: a wave
-      // adds them up first (eight segments of 32768 equal scores: 45 us by atomics alone, 20 us).
-      uint32_t zeros = 0u;
-      tiles([&](uint32_t t0) {
-        each_score(t0, [&](int j) {
-          const uint32_t b = bin_of(f[j]);
-          if (b == ONE_B)
-            ++zeros;
-          else
-            atomicAdd(&L.hist[b - ONE_B], 1u);
-        });
-      });
-      zeros = wave_reduce(zeros, 0u, [](uint32_t a, uint32_t b) { return a + b; });
-      if (lane == 0) atomicAdd(&L.hist[0], zeros);
-    }
-    __syncthreads();
-    if (wave == 0) {
-      const Pick p = pick_bucket<NB / 64>(L.hist, uint32_t(k), lane);
-      if (lane == 0) {
-        L.sh_key = p.digit;
-        L.sh_rem = p.rem;
-        L.sh_cnt = p.cnt;
-      }
-    }
-    __syncthreads();
-    const uint32_t bin = ONE_B + L.sh_key;
-    uint32_t rem = L.sh_rem, cnt = L.sh_cnt;   // T is the rem-th largest of the bin's cnt scores
-    uint32_t T = 0u;                           // its order key
+    uint32_t T = 0u;                // the threshold's order key,
+    uint32_t rem = 0u, cnt = 0u;    // the rem-th largest of the cnt scores looked at last
     {
+      constexpr uint32_t INF_B = 0x7f800000u, NINF_B = 0xff800000u;
+      const bool clean = hi_b <= INF_B && fin_b >= int32_t(FIN_SHIFT);   // uniform
+      float mn = __uint_as_float(lo_b), mx = __uint_as_float(uint32_t(fin_b) - FIN_SHIFT);
+      // the finite extremes of wave `lane`'s scores (wlo > whi: it has none)
+      const bool some = clean && fin_w >= int32_t(FIN_SHIFT);
+      float wlo = some ? __uint_as_float(lo_w) : INFINITY;
+      float whi = some ? __uint_as_float(uint32_t(fin_w) - FIN_SHIFT) : -INFINITY;
+      // this thread's finite scores that are in (past the end: NaN)
+      auto finite_extremes = [&](float& lo, float& hi, auto&& in) {
+        tiles([&](uint32_t t0) {
+#pragma unroll
+          for (int c = 0; c < CH; ++c) {
+            if (t0 + c * CHUNK >= uint32_t(n)) continue;   // uniform: nothing left
+#pragma unroll
+            for (int j = RCW * c; j < RCW * c + RCW; j += 2) {
+              const bool a = fabsf(f[j]) < INFINITY && in(f[j]);
+              const bool b = fabsf(f[j + 1]) < INFINITY && in(f[j + 1]);
+              lo = min3(lo, a ? f[j] : INFINITY, b ? f[j + 1] : INFINITY);
+              hi = max3(hi, a ? f[j] : -INFINITY, b ? f[j + 1] : -INFINITY);
+            }
+          }
+        });
+      };
+      // the waves' extremes of those, to red[3] and red[4] and back
+      auto leave_extremes = [&](float lo, float hi) {
+        const uint32_t r0 = wave_reduce(__float_as_uint(lo), INF_B, fmin_bits);
+        const uint32_t r1 = wave_reduce(__float_as_uint(hi), NINF_B, fmax_bits);
+        if (lane == 0) {
+          L.red[3][wave] = r0;
+          L.red[4][wave] = r1;
+        }
+      };
+      auto take_extremes = [&]() {
+        wlo = __uint_as_float(lane < NW ? L.red[3][lane] : INF_B);
+        whi = __uint_as_float(lane < NW ? L.red[4][lane] : NINF_B);
+        mn = __uint_as_float(row0_reduce(__float_as_uint(wlo), INF_B, fmin_bits));
+        mx = __uint_as_float(row0_reduce(__float_as_uint(whi), NINF_B, fmax_bits));
+      };
+      if (!clean) {
+        float lo = INFINITY, hi = -INFINITY;
+        finite_extremes(lo, hi, [](float) { return true; });
+        leave_extremes(lo, hi);
+        __syncthreads();
+        take_extremes();
+        if (mn > mx) mn = mx = 0.f;   // no finite score: -inf and NaN to bin 0, +inf to the last
+      }
+      // A few far scores (those of pinned or masked entries) would leave the others one bin: where the
+      // whole range is many times what every wave's scores cover, the bins cut that, half as much again
+      // to either side, and what lies beyond shares the first and the last bin.  (The first two waves'
+      // say whether to look: one of them, for entries pinned in one run.)
+      auto width = [&](int w) {
+        return __uint_as_float(uint32_t(__builtin_amdgcn_readlane(int(__float_as_uint(whi)), w))) -
+               __uint_as_float(uint32_t(__builtin_amdgcn_readlane(int(__float_as_uint(wlo)), w)));
+      };
+      if ((STREAM || NC < TILE) && mx - mn > 8.f * fminf(width(0), width(1))) {
+        const bool has = wlo <= whi;
+        const float chi = __uint_as_float(row0_reduce(has ? __float_as_uint(whi) : INF_B, INF_B, fmin_bits));
+        const float clo = __uint_as_float(row0_reduce(has ? __float_as_uint(wlo) : NINF_B, NINF_B, fmax_bits));
+        const float w = chi - clo;
+        if (w > 0.f && mx - mn > 8.f * w) {
+          mn = fmaxf(mn, clo - w);
+          mx = fminf(mx, chi + w);
+        }
+      }
+      uint32_t bin = 0u;
+      float inv, at;
+      // Bits of ONE + the bin: the sum's unit is 1.  NaN goes to bin 0: that of a score, and that of
+      // 0 times infinity or infinity less itself, which then takes every lower score with it.
+      auto bin_of = [&](float x) {
+        return __float_as_uint(__builtin_amdgcn_fmed3f(fmaf(x, inv, at), ONE, ONE + float(NB - 1)));
+      };
+      for (int level = 0;; ++level) {
+        inv = mn < mx ? float(NB - 2) / (mx - mn) : 1.f;
+        at = fmaf(-mn, inv, ONE);
+        tiles([&](uint32_t t0) {
+          // A bin that many scores share makes every lane's atomic wait for the others.  Such bins are
+          // the outermost ones (equal scores, a far value and all others, what lies beyond the range):
+          // where a wave's first scores show it, it adds them up in registers.
+          const uint32_t s = bin_of(f[0]);
+          const bool in = t0 + RCW * tid < uint32_t(n);
+          if (__popcll(__ballot(in && s - (ONE_B + 1) >= uint32_t(NB - 3))) < 6) {
+            each_score(t0, [&](int j) { atomicAdd(&L.hist[bin_of(f[j]) - ONE_B], 1u); });
+          } else {
+            const int n1 = __popcll(__ballot(in && s == ONE_B + NB - 2));
+            const int n2 = __popcll(__ballot(in && s == ONE_B + NB - 1));
+            const uint32_t top = n2 > n1 ? ONE_B + NB - 1 : ONE_B + NB - 2;
+            uint32_t c0 = 0u, c1 = 0u;
+            each_score(t0, [&](int j) {
+              const uint32_t b = bin_of(f[j]);
+              c0 += uint32_t(b == ONE_B);
+              c1 += uint32_t(b == top);
+              if (b != ONE_B && b != top) atomicAdd(&L.hist[b - ONE_B], 1u);
+            });
+            c0 = wave_reduce(c0, 0u, add_bits);
+            c1 = wave_reduce(c1, 0u, add_bits);
+            if (lane == 0) {
+              atomicAdd(&L.hist[0], c0);
+              atomicAdd(&L.hist[top - ONE_B], c1);
+            }
+          }
+        });
+        __syncthreads();
+        if (wave == 0) {
+          const Pick p = pick_bucket<NB / 64>(L.hist, uint32_t(k), lane);
+          if (lane == 0) {
+            L.sh_key = p.digit;
+            L.sh_rem = p.rem;
+            L.sh_cnt = p.cnt;
+          }
+        }
+        __syncthreads();
+        bin = ONE_B + L.sh_key;
+        rem = L.sh_rem;   // T is the rem-th largest of the bin's cnt scores
+        cnt = L.sh_cnt;
+        if (cnt <= uint32_t(NC) || mn == mx || level == 2) break;
+        // too many for the list (the range has a gap, or is that of a few scores): the bins anew, over
+        // the finite scores of this one
+        const float was = mx - mn;
+        float lo = INFINITY, hi = -INFINITY;
+        finite_extremes(lo, hi, [&](float x) { return bin_of(x) == bin; });
+        leave_extremes(lo, hi);
+        for (int i = tid; i < NB; i += NT) L.hist[i] = 0u;
+        __syncthreads();
+        take_extremes();
+        if (!(mn < mx && mx - mn < was)) break;   // equal, none, or no narrower: the bins stay
+      }
       auto here = [&](int j) { return bin_of(f[j]) == bin; };
       // T by block-wide digits of key - kmin (scores that are all equal leave no digit); each(visit)
       // visits this thread's keys of the bin

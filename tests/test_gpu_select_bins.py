@@ -1,7 +1,8 @@
 """Keep selection where its kernel changes: the sizes at which the next kernel takes over (1024,
 4096, 8192 and 32768 scores), the loads at the end of a segment (1 to 3 scores left, any start), and
 inputs that fill the threshold's bin beyond the ranked list (256), beyond the gathered list
-(4096), with equal scores, with NaN as the threshold and with ranges that overflow or vanish."""
+(4096), with equal scores, with NaN as the threshold, with ranges that overflow or vanish and with
+far values (pinned or masked entries) that widen the range; and what far values cost."""
 import numpy as np
 import pytest
 import torch
@@ -63,17 +64,64 @@ def _hostile(kind, n):
     elif kind == "zeros":
         x[r.random(n) < 0.7] = 0.0
         x[::3] = -0.0
+    elif kind == "far":           # one pinned entry
+        x[n // 3] = 1e9
+    elif kind == "far both":      # of several sizes, to either side
+        x[[1, n // 2, n - 2]] = 1e9, 1e4, -1e30
+    elif kind == "far run":       # more than one wave's entries
+        x[:min(n // 2, 700)] = 1e9
+    elif kind == "masked":
+        x[r.random(n) < 0.5] = -1e30
+    elif kind == "masked negative":
+        x = np.where(r.random(n) < 0.1, np.float32(-1e9), -x)
+    elif kind == "masked twice":
+        x = np.where(r.random(n) < 0.3, np.float32(1e30), np.where(r.random(n) < 0.3, np.float32(1e6), x))
+    elif kind == "masked infinite":
+        x[r.random(n) < 0.5] = -np.inf
     elif kind == "narrow band":   # thousands of different scores in one bin
         x = (11.0 + r.uniform(0.0, 1e-3, n)).astype(np.float32)
         x[::50] = r.uniform(0.0, 100.0, len(x[::50]))
-    else:                         # some hundreds in one bin
+    elif kind:                    # some hundreds in one bin
         x = np.where(np.arange(n) % 8 == 0, 11.0 + r.uniform(0.0, 1e-3, n), x).astype(np.float32)
     return x.astype(np.float32)
 
 
 @pytest.mark.parametrize("kind", ["equal", "equal and infinite", "nan", "only infinite", "overflowing range", "denormal",
-                                  "zeros", "narrow band", "cluster"])
+                                  "zeros", "narrow band", "cluster", "far", "far both", "far run", "masked",
+                                  "masked negative", "masked twice", "masked infinite"])
 def test_hostile_scores(kind):
     for n in (1000, 4001, 8000, 32768, 50001):
         print(f"[select] {kind} n={n}", flush=True)
         _check([_hostile(kind, n), _hostile(kind, n // 2)], (0.0, 0.2, 0.5, 0.9))
+
+
+def test_one_value():
+    for v in (0.0, 7.5, np.inf, -np.inf, np.nan):
+        _check([np.full(n, v, np.float32) for n in (5, 4000, 8192, 32768, 40000)], (0.0, 0.3, 0.9))
+
+
+@pytest.mark.parametrize("kind", ["far", "far both", "masked", "masked negative", "masked infinite"])
+def test_far_values_cost(kind):
+    """Far values may not leave the other scores one bin, on which every lane's atomic waits for the
+    others: at most 2.5 times the time of plain scores (1.1 to 1.7 measured; 2.1 to 4.3 with bins over
+    the whole range)."""
+    from paper_2607_27600_amd import cc
+    n, segs, k = 32768, 8, 4096
+    keep = torch.empty(segs * k, dtype=torch.int32, device="cuda")
+
+    def best(x):
+        s = torch.from_numpy(np.concatenate([x] * segs)).cuda()
+        call = lambda: cc.cc_select_keep(s, [i * n for i in range(segs)], [n] * segs, [k] * segs, keep)
+        call()
+        t = []
+        for _ in range(7):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(40):
+                call()
+            b.record()
+            torch.cuda.synchronize()
+            t.append(a.elapsed_time(b))
+        return min(t)
+
+    assert best(_hostile(kind, n)) <= 2.5 * best(_hostile("", n))
