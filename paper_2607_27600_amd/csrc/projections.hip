@@ -192,6 +192,7 @@ struct TilePlan {
 TilePlan plan_tiles(int M, int N, int K, bool may_split) {
   const int64_t nk = K / 64;
   TilePlan best{0, 1};
+  if (M == 0 || N == 0) return best;   // an empty cache: no tiles
   double best_us = 1e300;
   for (int i = 0; i < kNShapes; ++i) {
     const int tm = 32 * kShapes[i].mb, tn = 64 * kShapes[i].nb;

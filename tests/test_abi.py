@@ -5,6 +5,7 @@ import ctypes
 import os
 import re
 import subprocess
+import sys
 
 import pytest
 
@@ -101,6 +102,19 @@ def test_workspace_queries_and_validation():
     assert lib.cc_select_workspace(-1, ctypes.byref(n)) == cc.CC_ERR_ARG
     assert lib.cc_compact_workspace(ctypes.byref(p), 32, 1, ctypes.byref(n)) == cc.CC_OK
     assert lib.cc_compact_workspace(ctypes.byref(p), 32, 2, ctypes.byref(n)) == cc.CC_ERR_ARG
+
+
+@pytest.mark.parametrize("mode", ["last_layer", "last_layer_fused", "last_layer_h", "full"])
+@pytest.mark.parametrize("cu,D,F", [([0, 0], 64, 64), ([0, 0], 4096, 14336), ([0, 0, 0], 512, 64)])
+def test_an_empty_cache_needs_no_workspace(mode, cu, D, F):
+    """In a process of its own: a division by the number of tiles would end it."""
+    prog = ("from paper_2607_27600_amd import cc\n"
+            f"p = cc.problem(dtype='bf16', cu_seqlens={cu}, n_heads_q=2, n_heads_kv=1, head_dim=128, hidden={D},\n"
+            f"               vocab=1024, device='cpu', mode='{mode}', n_layers=2, ffn={F}, rope_theta=1e4,\n"
+            "               rms_eps=1e-5)\n"
+            "print(cc.cc_score_workspace(p))\n")
+    r = subprocess.run([sys.executable, "-c", prog], capture_output=True, text=True, cwd=ROOT)
+    assert r.returncode == 0 and r.stdout.split()[-1] == "0", (r.returncode, r.stderr[-300:])
 
 
 def test_calls_with_bad_arguments_enqueue_nothing():
