@@ -443,19 +443,21 @@ def cc_select_workspace(n_segs: int) -> int:
 
 
 def _host_array(x, dtype, ctype):
-    """x as a C array of integers to pass by pointer: a plain short list or tuple of ints directly,
-    anything else through a C-contiguous numpy array (no copy if it is one of that type).  Up to
-    64 ints are quicker as a C array (8: 1 us against 3 to 5), from 128 on through numpy (1024:
-    67 us against 38)."""
+    """x as a C array of integers to pass by pointer, and its length: a plain short list or tuple of
+    ints directly, anything else (a scalar, ints that do not fit) through a C-contiguous numpy array
+    (no copy if it is one of that type).  Up to 64 ints are quicker as a C array (8: 1 us against 3 to
+    5), from 128 on through numpy (1024: 67 us against 38)."""
     if type(x) in (list, tuple) and len(x) <= 64:
         try:
-            return (ctype * len(x))(*x)
+            arr = (ctype * len(x))(*x)
+            if arr[:] == list(x):   # ctypes wraps what does not fit
+                return arr, len(x)
         except TypeError:
             pass
     a = np.ascontiguousarray(np.asarray(x), dtype=dtype)
     arr = ctypes.cast(a.ctypes.data, ctypes.POINTER(ctype))
     arr._keep = a
-    return arr
+    return arr, len(a)
 
 
 def cc_select_keep(scores: torch.Tensor, seg_start: Sequence[int], seg_len: Sequence[int],
@@ -463,10 +465,9 @@ def cc_select_keep(scores: torch.Tensor, seg_start: Sequence[int], seg_len: Sequ
                    workspace: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """seg_start, seg_len, k: host sequences or numpy arrays (int64, int32, int32 arrays
     are passed without a copy)."""
-    st = _host_array(seg_start, np.int64, _i64)
-    ln = _host_array(seg_len, np.int32, _i32)
-    kk = _host_array(k, np.int32, _i32)
-    n = len(seg_len)
+    st, _ = _host_array(seg_start, np.int64, _i64)
+    ln, n = _host_array(seg_len, np.int32, _i32)
+    kk, _ = _host_array(k, np.int32, _i32)
     if workspace is None:
         workspace = _workspace(cc_select_workspace(n), scores.device)
     _check(_lib.cc_select_keep(_ptr(scores), n, st, ln, kk, _ptr(keep_idx), _ptr(workspace),

@@ -253,3 +253,30 @@ def test_packed_lmhead_entry_points_validate_on_the_host():
                                       ws, big, None) == cc.CC_ERR_ARG
     assert lib.cc_lmhead_score(ctypes.byref(p), dummy, dummy, dummy, dummy, None, ws, big,
                                None) == cc.CC_ERR_ARG
+
+
+def test_selection_takes_scalars_and_refuses_what_does_not_fit(monkeypatch):
+    """Every form of the host lists reaches the library, whose host checks then refuse the budgets
+    (k > length), or raises what numpy raises for it."""
+    import numpy as np
+    import torch
+    from paper_2607_27600_amd import cc
+    monkeypatch.setattr(cc, "_stream", lambda stream=None: None)
+    t = torch.zeros(64)
+    ws = torch.empty(4096, dtype=torch.uint8)
+
+    def status(start, length, k):
+        with pytest.raises(cc.CCError) as e:
+            cc.cc_select_keep(t, start, length, k, t.int(), workspace=ws)
+        return e.value.status
+
+    for start, length, k in [([0], [5], [7]), ((0, 5), (5, 5), (1, 7)), (0, 5, 7), (np.int64(0), np.int32(5), 7),
+                             ([np.int64(0)], [np.int32(5)], [np.int32(7)]), ([0.0], [5.0], [7.0]), ([0], [5], [True + 6]),
+                             (np.zeros(1, np.int64), np.array([5], np.int32), np.array([7], np.int32)),
+                             (range(2), [5] * 2, [7] * 2), ([0] * 100, [5] * 100, [7] * 100),
+                             (torch.zeros(1, dtype=torch.int64), torch.tensor([5]), torch.tensor([7]))]:
+        assert status(start, length, k) == cc.CC_ERR_SHAPE, (start, length, k)
+    for bad in ([2 ** 64 + 1], [2 ** 70]):
+        with pytest.raises(OverflowError):
+            cc.cc_select_keep(t, [0], [5], bad, t.int(), workspace=ws)
+    assert [list(cc._host_array(x, np.int64, cc._i64)[0][:2]) for x in ([3, 2 ** 40], np.array([3, 2 ** 40]))] == [[3, 2 ** 40]] * 2
