@@ -189,7 +189,12 @@ def problem(*, dtype: str, cu_seqlens: Sequence[int], n_heads_q: int, n_heads_kv
     """cu_device: the int32 values of cu_seqlens already on the device (the default copies
     them there and waits for the copy, so the problem may be used on any stream)."""
     cu_h = torch.as_tensor(list(cu_seqlens), dtype=torch.int32).contiguous()
-    cu_d = cu_h.to(device) if cu_device is None else cu_device
+    if cu_device is None:
+        cu_d = cu_h.to(device)
+    elif cu_device.dtype != torch.int32 or cu_device.shape != cu_h.shape or not cu_device.is_contiguous():
+        raise ValueError("cu_device must hold the values of cu_seqlens as contiguous int32")
+    else:
+        cu_d = cu_device
     s = c_problem()
     s.dtype = {"f32": CC_F32, "bf16": CC_BF16}[dtype]
     s.mode = {"last_layer": CC_MODE_LAST_LAYER, "full": CC_MODE_FULL,

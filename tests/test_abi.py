@@ -280,3 +280,15 @@ def test_selection_takes_scalars_and_refuses_what_does_not_fit(monkeypatch):
         with pytest.raises(OverflowError):
             cc.cc_select_keep(t, [0], [5], bad, t.int(), workspace=ws)
     assert [list(cc._host_array(x, np.int64, cc._i64)[0][:2]) for x in ([3, 2 ** 40], np.array([3, 2 ** 40]))] == [[3, 2 ** 40]] * 2
+
+
+def test_device_lengths_that_the_kernels_would_misread_are_refused():
+    import torch
+    from paper_2607_27600_amd import cc
+    kw = dict(dtype="bf16", cu_seqlens=[0, 5, 9], n_heads_q=1, n_heads_kv=1, head_dim=64, hidden=64, vocab=64,
+              device="cpu")
+    cu = torch.tensor([0, 5, 9], dtype=torch.int32)
+    assert cc.problem(cu_device=cu, **kw).cu_d is cu
+    for bad in (cu.long(), cu[:2], cu.view(1, 3), torch.zeros(6, dtype=torch.int32)[::2]):
+        with pytest.raises(ValueError):
+            cc.problem(cu_device=bad, **kw)
