@@ -32,6 +32,12 @@
  *   - Element types: CC_BF16 tensors are bfloat16, CC_F32 tensors are float32;
  *     scores are always float32.  Matrices are row-major.
  *   - Calls that share a workspace must be ordered (same stream or synchronised).
+ *   - The same call repeats bit for bit.  An entry's results do not depend on the entries beside it
+ *     beyond that, except in rounding: attention sums a row's keys in one or two chains (fp32: in
+ *     four or eight) by the size of the launch, and the projections of FULL and LAST_LAYER_H cut
+ *     their sums by the number of entries.  A sequence scored alone and in a batch can therefore
+ *     differ in the last bits, and a selection with it where scores nearly tie.  cc_linear and the LM
+ *     head calls on the same rows, selection and compaction do not depend on the batch at all.
  */
 #ifndef CC_H
 #define CC_H

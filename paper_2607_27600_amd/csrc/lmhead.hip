@@ -268,12 +268,14 @@ __global__ __launch_bounds__(256) void quantize_matrix_kernel(const T* __restric
 // exponentials), and few entries take E = 4, for four times the workgroups; beyond, E = 16 reads
 // whole cache lines.  Fold tile by tile in E = 16 -> now: 512 entries of 594 tiles 9.4 -> 6.2 us,
 // 200 entries of 501 tiles 8.6 -> 4.6, 4096 entries (E = 16) 10.0 -> 6.9.
+// The groups fold in one order for either E (pairs, pairs of pairs, up to 16 groups, then the four
+// sums), so that the scores of an entry are the same bits whatever the number of entries beside it.
 constexpr int CMB_G = 64;
 
 // (M, S) += (m, s): S is the sum of exponentials against the maximum M.
 __device__ __forceinline__ void lse_fold(float& M, float& S, float m, float s) {
   const float t = fmaxf(M, m), ref = t == -INFINITY ? 0.f : t;
-  S = S * expf(M - ref) + s * expf(m - ref);
+  S = fmaf(S, expf(M - ref), s * expf(m - ref));   // (written out: the contraction is part of the order)
   M = t;
 }
 
@@ -286,7 +288,7 @@ __device__ __forceinline__ void lse_fold(float& M, float& S, const float2 (&p)[Q
   const float ref = t == -INFINITY ? 0.f : t;
   float sum = S * expf(M - ref);
 #pragma unroll
-  for (int q = 0; q < Q; ++q) sum += p[q].y * expf(p[q].x - ref);
+  for (int q = 0; q < Q; ++q) sum = fmaf(p[q].y, expf(p[q].x - ref), sum);
   S = sum;
   M = t;
 }
@@ -335,9 +337,19 @@ __global__ __launch_bounds__(E * CMB_G) void lse_combine(const float2* partial, 
   if ((threadIdx.x & 63) < E) red[threadIdx.x >> 6][e] = make_float2(M, S);
   __syncthreads();
   if (writer) {
-    float2 p[NWV];
+    constexpr int W = NWV / 4;   // waves that share 16 groups
+    float2 p[4];
 #pragma unroll
-    for (int r = 0; r < NWV; ++r) p[r] = red[r][e];
+    for (int r = 0; r < 4; ++r) {
+      float2 w[W];
+#pragma unroll
+      for (int i = 0; i < W; ++i) w[i] = red[r * W + i][e];
+#pragma unroll
+      for (int off = 1; off < W; off <<= 1)
+#pragma unroll
+        for (int i = 0; i < W; i += 2 * off) lse_fold(w[i].x, w[i].y, w[i + off].x, w[i + off].y);
+      p[r] = w[0];
+    }
     M = -INFINITY;
     S = 0.f;
     lse_fold(M, S, p);
