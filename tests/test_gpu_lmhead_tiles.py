@@ -1,8 +1,16 @@
-"""The LM head over batches of different sizes: an entry's neighbours may change nothing."""
+"""The LM head at every tile width of its dispatch (64, 128, 192 and 256 entries), on row-major,
+packed and E4M3 weights, with dense random operands: fewer k-tiles than a ring holds, as many, and
+enough for every ring to wrap twice; a vocabulary edge; both orders of tiles.  And what an entry's
+neighbours may change: nothing."""
+import numpy as np
 import pytest
 import torch
 
+from oracle import cc_oracle as O
+
 pytestmark = pytest.mark.gpu
+
+V = 700   # two whole vocabulary tiles and an edge
 
 
 def _operands(N, D, vocab, seed, std=0.05):
@@ -33,6 +41,39 @@ def _run(form, u, w, ids, cu=None):
         cc.cc_lmhead_score_fp8(p, u, codes, scale, ids, s, lse)
         return s, lse, codes, scale
     return s, lse
+
+
+def _e4m3(codes):
+    return torch.as_tensor(codes).view(torch.float8_e4m3fn).double()
+
+
+@pytest.mark.parametrize("k_tiles", [1, 3, 4, 11])
+@pytest.mark.parametrize("N", [1, 37, 64, 77, 129, 300, 641, 1500])
+@pytest.mark.parametrize("form", ["row", "packed", "fp8"])
+def test_against_fp64(form, N, k_tiles):
+    D = (128 if form == "fp8" else 64) * k_tiles
+    print(f"[lmhead tiles] {form} N={N} D={D}", flush=True)
+    u, w, ids = _operands(N, D, V, N + D)
+    s, lse, *q = _run(form, u, w, ids)
+    if q:
+        assert np.array_equal(q[0].cpu().numpy(), O.quantize_fp8(w.float().cpu().numpy(), per_row=False)[0])
+        uc, us = O.quantize_fp8(u.float().cpu().numpy(), per_row=True)
+        a = _e4m3(uc) * torch.as_tensor(us).double()[:, None]
+        b = _e4m3(q[0].cpu()) * q[1].cpu().double()
+    else:
+        a, b = u.cpu().double(), w.cpu().double()
+    z = a @ b.t().contiguous()
+    ref = torch.logsumexp(z, 1)
+    target = z[torch.arange(N), ids.cpu().long()]
+    # D fp32 additions of products that are exact (two roundings more for the scales of E4M3); then
+    # exponentials, sums and the logarithm of the result, some ulps of it
+    bound = (D + 2) * 2.0 ** -24 * (a.abs() @ b.abs().t().contiguous()).amax(1) + 2.0 ** -22 * ref.abs() + 4e-6
+    err = (lse.cpu().double() - ref).abs()
+    assert (err <= bound).all(), float((err / bound).max())
+    got, want = s.cpu().double(), (ref - target).clamp(min=0)
+    assert got[-1] == np.inf
+    err = (got - want).abs()[:-1]
+    assert (err <= 2 * bound[:-1]).all(), float((err / bound[:-1]).max())
 
 
 @pytest.mark.parametrize("form", ["row", "packed", "fp8", "f32"])
