@@ -53,7 +53,7 @@ cc_status check_problem(const cc_problem* p) {
   if (p->mode == CC_MODE_FULL || p->mode == CC_MODE_LAST_LAYER_H) {
     if ((p->mode == CC_MODE_FULL && p->n_layers < 1) || p->ffn < 1) return CC_ERR_SHAPE;
     if (p->dtype != CC_BF16) return CC_ERR_UNSUPPORTED;
-    // the W_q epilogue applies RoPE with one wave's 128 rows spanning exactly one head
+    // the W_q epilogue rotates pairs 64 rows apart, the halves of a 128-wide head
     if (p->head_dim != 128) return CC_ERR_UNSUPPORTED;
     if (p->ffn % 64 != 0) return CC_ERR_UNSUPPORTED;
     if (!(p->rope_theta > 0.f) || !(p->rms_eps >= 0.f)) return CC_ERR_ARG;
@@ -161,16 +161,12 @@ int lmhead_k(const cc_problem* p) {
   return p->mode == CC_MODE_LAST_LAYER_FUSED ? p->n_heads_q * p->head_dim : p->hidden;
 }
 
-// LM-head workspace: per-(vocabulary tile, entry) partials and target logits.  The size asked
-// of a caller with a packed weight also covers a packed copy of the entry rows; the kernels
-// read the rows as they are, the size is part of the interface.
+// What an LM head call needs: per-(vocabulary tile, entry) partials and target logits.
 size_t lmhead_ws_bytes(const cc_problem* p) {
   const size_t N = n_tokens(p);
   const int vt = lmhead_vocab_tile(p->dtype);
   const size_t n_vt = (p->vocab + vt - 1) / vt;
-  size_t b = align_up(n_vt * N * sizeof(float2)) + align_up(N * sizeof(float));
-  if (p->lmhead_packed) b += align_up(packed_rows_bytes(int64_t(N), lmhead_k(p)));
-  return b;
+  return align_up(n_vt * N * sizeof(float2)) + align_up(N * sizeof(float));
 }
 
 struct ScoreLayout {
@@ -463,6 +459,9 @@ cc_status cc_lmhead_workspace(const cc_problem* p, size_t* bytes) {
   if (!bytes) return CC_ERR_ARG;
   CC_TRY(check_problem(p));
   *bytes = lmhead_ws_bytes(p);
+  // Of a packed problem the query has always covered a packed copy of the entry rows as well.  The
+  // calls need no more than the above, and cc_score_workspace asks for no more.
+  if (p->lmhead_packed) *bytes += align_up(packed_rows_bytes(n_tokens(p), lmhead_k(p)));
   return CC_OK;
 }
 
@@ -772,15 +771,8 @@ cc_status cc_select_keep(const float* scores, int32_t n_segs, const int64_t* seg
 // ------------------------------------------------------------------ compaction
 
 namespace {
-// Bytes of the planning tables the compaction was first built with ({seq, layer, head, list}
-// of 16 bytes a plane); the lists, all that is uploaded (when they do not fit the kernel
-// arguments), always fit.  The size is part of the interface.
-size_t compact_ws_bytes_for(const cc_problem* p, int per_head, int n_layers) {
-  const size_t n_lists = size_t(p->n_seqs) * (per_head ? p->n_heads_kv : 1);
-  const size_t n_planes = size_t(p->n_seqs) * n_layers * p->n_heads_kv;
-  return align_up(n_lists * sizeof(CompactList)) + align_up(n_planes * 16) +
-         align_up(size_t(p->n_seqs) * sizeof(int32_t));
-}
+// Room for the keep lists, which are uploaded when they do not fit the kernel arguments.
+size_t compact_ws_bytes(size_t n_lists) { return align_up(n_lists * sizeof(CompactList)); }
 
 // The lists of a compaction in the order the kernels want: sequences by falling budget (of
 // the longest list of each), heads in order.  per: lists a sequence; take: lists kept of them
@@ -832,7 +824,7 @@ cc_status cc_compact_workspace(const cc_problem* p, int32_t cache_layers, int32_
   CC_TRY(check_problem(p));
   if (per_head != 0 && per_head != 1) return CC_ERR_ARG;
   if (cache_layers < 1) return CC_ERR_ARG;
-  *bytes = compact_ws_bytes_for(p, per_head, cache_layers);
+  *bytes = compact_ws_bytes(size_t(p->n_seqs) * (per_head ? p->n_heads_kv : 1));
   return CC_OK;
 }
 
@@ -858,7 +850,7 @@ cc_status cc_compact_kv(const cc_problem* p, const cc_kv* kv, const int32_t* kee
   int64_t off = 0;
   CC_TRY(compact_lists(p, k_h, per, per, false, lists, max_k, off));
   if (off > 0 && !keep_idx) return CC_ERR_ARG;
-  CC_TRY(check_ws(ws, ws_bytes, compact_ws_bytes_for(p, per_head, kv->n_layers)));
+  CC_TRY(check_ws(ws, ws_bytes, compact_ws_bytes(lists.size())));
   hipStream_t s = static_cast<hipStream_t>(stream);
   CompactLaunch c;
   c.n_tensors = 2;
@@ -892,10 +884,6 @@ int rows_slab_bytes(int row_bytes) {
   while (slab > 16 && row_bytes % slab != 0) slab >>= 1;
   return slab;
 }
-size_t rows_ws_bytes(const cc_problem* p, int row_bytes) {
-  const size_t n_slabs = size_t(row_bytes / rows_slab_bytes(row_bytes));
-  return align_up(size_t(p->n_seqs) * sizeof(CompactList)) + align_up(size_t(p->n_seqs) * n_slabs * 16);
-}
 }  // namespace
 
 cc_status cc_compact_rows_workspace(const cc_problem* p, int32_t row_bytes, int32_t per_head,
@@ -904,7 +892,7 @@ cc_status cc_compact_rows_workspace(const cc_problem* p, int32_t row_bytes, int3
   CC_TRY(check_problem(p));
   if (per_head != 0 && per_head != 1) return CC_ERR_ARG;
   if (row_bytes < 16 || row_bytes % 16 != 0) return CC_ERR_UNSUPPORTED;
-  *bytes = rows_ws_bytes(p, row_bytes);
+  *bytes = compact_ws_bytes(p->n_seqs);
   return CC_OK;
 }
 
@@ -923,7 +911,7 @@ cc_status cc_compact_rows(const cc_problem* p, void* rows, int32_t row_bytes,
   CC_TRY(compact_lists(p, k_h, per_head ? hkv : 1, 1, true, lists, max_k, off));
   if (off > 0 && (!keep_idx || !rows)) return CC_ERR_ARG;
   if ((rows && !aligned16(rows)) || (out_rows && !aligned16(out_rows))) return CC_ERR_ARG;
-  CC_TRY(check_ws(ws, ws_bytes, rows_ws_bytes(p, row_bytes)));
+  CC_TRY(check_ws(ws, ws_bytes, compact_ws_bytes(lists.size())));
   if (max_k == 0) return CC_OK;
   hipStream_t s = static_cast<hipStream_t>(stream);
   auto view = [&](void* base) {

@@ -292,3 +292,26 @@ def test_device_lengths_that_the_kernels_would_misread_are_refused():
     for bad in (cu.long(), cu[:2], cu.view(1, 3), torch.zeros(6, dtype=torch.int32)[::2]):
         with pytest.raises(ValueError):
             cc.problem(cu_device=bad, **kw)
+
+
+@pytest.mark.parametrize("mode", ["last_layer", "last_layer_fused", "last_layer_h", "full"])
+def test_workspace_holds_no_tables_that_nothing_writes(mode):
+    """A packed weight adds nothing to a score's workspace (the entry rows are read as they are), and
+    compaction needs its keep lists (32 bytes or fewer each), whatever the layers and slabs."""
+    from paper_2607_27600_amd import cc
+    n = ctypes.c_size_t()
+    modes = {"last_layer": 0, "full": 1, "last_layer_h": 2, "last_layer_fused": 3}
+    kw = dict(mode=modes[mode], n_layers=2, ffn=1024, rope_theta=1e4, rms_eps=1e-5)
+    sizes = []
+    for packed in (0, 1):
+        p, _k = _prob(lmhead_packed=packed, **kw)
+        assert cc._lib.cc_score_workspace(ctypes.byref(p), ctypes.byref(n)) == cc.CC_OK
+        sizes.append(n.value)
+    assert sizes[0] == sizes[1] > 0
+    for per_head in (0, 1):
+        lists = p.n_seqs * (p.n_heads_kv if per_head else 1)
+        for layers in (1, 80):
+            assert cc._lib.cc_compact_workspace(ctypes.byref(p), layers, per_head, ctypes.byref(n)) == cc.CC_OK
+            assert 24 * lists <= n.value <= 32 * lists + 256
+        assert cc._lib.cc_compact_rows_workspace(ctypes.byref(p), 1 << 20, per_head, ctypes.byref(n)) == cc.CC_OK
+        assert 24 * p.n_seqs <= n.value <= 32 * p.n_seqs + 256
