@@ -198,18 +198,16 @@ def flushed_ms(fn, reps: int, flush) -> float:
 
 def lmhead_traffic(cfg_name: str):
     """HBM bytes per LM-head launch from the committed counter summary of this workload,
-    or None when there is none or the GEMM source has changed since it was taken."""
-    import hashlib
+    or None when there is none or the LM head's sources have changed since it was taken."""
+    from paper_2607_27600_amd.pmc_summary import lmhead_sources_sha256
     path = os.path.join(ROOT, "profiles", f"lmhead_{cfg_name.lower()}_traffic.json")
-    src = os.path.join(ROOT, "paper_2607_27600_amd", "csrc", "gemm_tile.h")
     try:
         with open(path) as f:
             rec = json.load(f)
-        with open(src, "rb") as f:
-            digest = hashlib.sha256(f.read()).hexdigest()
+        digest = lmhead_sources_sha256(os.path.join(ROOT, "paper_2607_27600_amd", "csrc"))
     except OSError:
         return None
-    return rec.get("bytes_per_launch") if rec.get("gemm_source_sha256") == digest else None
+    return rec.get("bytes_per_launch") if rec.get("lmhead_sources_sha256") == digest else None
 
 
 def select_sweep(dev, flush, reps: int = 5) -> dict:
@@ -428,7 +426,7 @@ def bench_config(args, name: str, dev, with_extras: bool) -> dict:
         lm_tflops = lm_flop / (part["lmhead_lse"] * 1e-3) / 1e12
         res["roofline"] = {
             "kernel": "LM head on packed operands with the fused log-sum-exp and target gather "
-                      "(gemm_tile<8, 4, 3, 2, A_PACKED, EpiLse> + lse_combine)",
+                      "(gemm_tile in mode A_PACKED with EpiLse, tile width by entries, + lse_combine)",
             "bound": "mfma", "achieved": lm_tflops, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
             "frac": lm_tflops / PEAK_BF16_TFLOPS, "traffic": lmhead_traffic(name),
             "flop_per_launch": lm_flop}

@@ -16,8 +16,8 @@ issue statistics per kernel: see issue().
 
 FETCH_SIZE / WRITE_SIZE are in KiB per dispatch.  The driver also copies 1 GiB device to
 device; each counter is scaled by (1 GiB / what it reads for that copy), so the figures are
-calibrated against a transfer of known size.  The record carries the sha256 of gemm_tile.h;
-bench.py reports the traffic only while the source matches.
+calibrated against a transfer of known size.  The record carries the sha256 of the sources that
+decide the traffic (gemm_tile.h and lmhead.hip); bench.py reports it only while they match.
 """
 from __future__ import annotations
 
@@ -28,6 +28,16 @@ import os
 import sys
 
 GIB_KIB = 1 << 20
+
+
+def lmhead_sources_sha256(csrc: str) -> str:
+    """Of what decides the LM head's traffic: the tiles with their loads and order, and the tile
+    width, rings and epilogue chosen for them."""
+    h = hashlib.sha256()
+    for name in ("gemm_tile.h", "lmhead.hip"):
+        with open(os.path.join(csrc, name), "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
 
 
 def _per_dispatch(path: str, counter: str) -> list:
@@ -58,11 +68,11 @@ def main(fetch_dir: str, write_dir: str, out: str, cfg_name: str = "C5") -> None
     f_copy = max(_find(f_rows, is_copy))
     w_copy = max(_find(w_rows, is_copy))
     f_lm = _find(f_rows, is_lm)[-1]
+    kernel = [n for n, _ in f_rows if is_lm(n)][-1].split("(")[0].removeprefix("void ")
     w_lm = _find(w_rows, is_lm)[-1]
     kf, kw = GIB_KIB / f_copy, GIB_KIB / w_copy
     here = os.path.dirname(os.path.abspath(__file__))
-    with open(os.path.join(here, "csrc", "gemm_tile.h"), "rb") as fh:
-        digest = hashlib.sha256(fh.read()).hexdigest()
+    digest = lmhead_sources_sha256(os.path.join(here, "csrc"))
     sys.path.insert(0, os.path.dirname(here))
     from synth import configs as C
     cfg = C.CONFIGS[cfg_name]
@@ -70,8 +80,8 @@ def main(fetch_dir: str, write_dir: str, out: str, cfg_name: str = "C5") -> None
     vt = (V + 255) // 256
     alg = 2 * V * D + 2 * N * D + 8 * vt * N + 4 * N
     rec = {
-        "kernel": f"gemm_tile<8, 4, 3, 2, A_PACKED, EpiLse> (LM head on the packed weight + fused "
-                  f"log-sum-exp and target gather), {cfg_name} shapes",
+        "kernel": f"{kernel} (LM head on the packed weight, fused log-sum-exp and target gather), "
+                  f"{cfg_name} shapes",
         "fetch_kib_raw": f_lm, "write_kib_raw": w_lm,
         "copy_fetch_kib_raw": f_copy, "copy_write_kib_raw": w_copy,
         "fetch_scale": kf, "write_scale": kw,
@@ -80,7 +90,7 @@ def main(fetch_dir: str, write_dir: str, out: str, cfg_name: str = "C5") -> None
         "algorithmic_bytes_note": f"W_lm {V}x{D} bf16 (packed) + U {N}x{D} bf16 read + "
                                   f"partials {vt}x{N}x8 B and target logits {N}x4 B written",
         "traffic_over_algorithmic": (f_lm * kf + w_lm * kw) * 1024.0 / alg,
-        "gemm_source_sha256": digest,
+        "lmhead_sources_sha256": digest,
     }
     with open(out, "w") as fh:
         json.dump(rec, fh, indent=1)

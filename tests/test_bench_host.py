@@ -44,3 +44,24 @@ def test_row_work_model_matches_the_algorithmic_counts():
                 "full": cfg.n_layers * (per_layer + att) + lm}[cfg.mode]
         got = bench._row_flops(cfg, np.arange(N)).sum()
         assert abs(got - want) <= 1e-9 * want, (name, got, want)
+
+
+def test_traffic_is_reported_only_for_the_sources_it_was_taken_on(tmp_path, monkeypatch):
+    import json
+    import bench
+    from paper_2607_27600_amd.pmc_summary import lmhead_sources_sha256
+    csrc = tmp_path / "paper_2607_27600_amd" / "csrc"
+    csrc.mkdir(parents=True)
+    (tmp_path / "profiles").mkdir()
+    files = {"gemm_tile.h": b"tiles", "lmhead.hip": b"epilogue"}
+    for name, text in files.items():
+        (csrc / name).write_bytes(text)
+    (tmp_path / "profiles" / "lmhead_c5_traffic.json").write_text(
+        json.dumps({"bytes_per_launch": 7.0, "lmhead_sources_sha256": lmhead_sources_sha256(str(csrc))}))
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    assert bench.lmhead_traffic("C5") == 7.0 and bench.lmhead_traffic("C2") is None
+    for name, text in files.items():
+        (csrc / name).write_bytes(text + b" changed")
+        assert bench.lmhead_traffic("C5") is None, name
+        (csrc / name).write_bytes(text)
+    assert bench.lmhead_traffic("C5") == 7.0
