@@ -622,7 +622,7 @@ hipError_t launch_attention(const AttnLaunch& a, hipStream_t s) {
   if (a.n_work == 0) return hipSuccess;
   if (a.dtype != CC_BF16) return launch_attention_f32(a, s);
   // a table stands for more than ATTN_INLINE sequences: many items
-  if (a.items.table) return launch_bf16<1>(a, a.items, s);
+  if (a.table.table) return launch_bf16<1>(a, a.table, s);
   // Two key groups where the longest chain of tiles, not the sum of all, makes the launch's length:
   // up to one item a CU (two groups fill it) from 12 tiles on, up to two items a CU (one group each
   // would fill it, but the short ones leave early) from 12 to 28 tiles on.  One group against two:

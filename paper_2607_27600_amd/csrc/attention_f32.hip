@@ -242,12 +242,11 @@ hipError_t launch_f32(const AttnLaunch& a, const Items& items, hipStream_t s) {
 }
 
 // Eight waves an item where the launch leaves CUs idle and an item has tiles to share.  (At head dim
-// 128 eight waves leave each too few registers.  Tables stand for more than ATTN_INLINE sequences:
-// many items.)
+// 128 eight waves leave each too few registers.)
 template <class Items>
 hipError_t launch_f32(const AttnLaunch& a, const Items& items, hipStream_t s) {
   if (a.head_dim != 64) return launch_f32<128, 4>(a, items, s);
-  const bool wide = !a.items.table && a.n_work <= 256 && a.items.seqs[0].n >= 8 * F_BN;
+  const bool wide = a.n_work <= 256 && a.items.seqs[0].n >= 8 * F_BN;
   return wide ? launch_f32<64, 8>(a, items, s) : launch_f32<64, 4>(a, items, s);
 }
 
@@ -256,7 +255,9 @@ hipError_t launch_f32(const AttnLaunch& a, const Items& items, hipStream_t s) {
 int attention_f32_rows() { return F_ROWS; }
 
 hipError_t launch_attention_f32(const AttnLaunch& a, hipStream_t s) {
-  if (!a.items.table && a.items.n_seqs == 1)
+  if (a.table.table)   // more than ATTN_INLINE sequences: many items
+    return a.head_dim != 64 ? launch_f32<128, 4>(a, a.table, s) : launch_f32<64, 4>(a, a.table, s);
+  if (a.items.n_seqs == 1)
     return launch_f32(a, AttnOne{a.items.nkv, a.items.seqs[0].n}, s);
   return launch_f32(a, a.items, s);
 }

@@ -236,8 +236,7 @@ char* at(void* ws, size_t off) { return static_cast<char*>(ws) + off; }
 cc_status run_attention(const cc_problem* p, const void* q, const cc_kv* kv, int layer, void* o,
                         void* ws, hipStream_t s, bool upload = true) {
   AttnLaunch a;
-  a.items.table = nullptr;
-  a.items.cu = p->cu_seqlens_d;
+  a.table = AttnTable{nullptr, p->cu_seqlens_d};
   a.items.nkv = p->n_heads_kv;
   a.items.n_seqs = 0;
   if (p->n_seqs <= ATTN_INLINE) {
@@ -257,7 +256,7 @@ cc_status run_attention(const cc_problem* p, const void* q, const cc_kv* kv, int
     const std::vector<int4> work = attention_work(p);
     if (upload && !work.empty())
       CC_HIP(hipMemcpyAsync(ws, work.data(), work.size() * sizeof(int4), hipMemcpyHostToDevice, s));
-    a.items.table = static_cast<const int4*>(ws);
+    a.table.table = static_cast<const int4*>(ws);
     a.n_work = int(work.size());
   }
   if (a.n_work == 0) return CC_OK;

@@ -82,23 +82,15 @@ struct AttnOne {
 };
 // Up to ATTN_INLINE sequences travel by value, longest first, and a block finds its item with a
 // few scalar steps (an uploaded table, read before the sequence bounds, costs a call 2 to 3 us
-// more: 41 against 43 us for five ragged sequences of 5212 entries and 16 heads of 64); more
-// sequences use a table of {seq, KV head, row block, 0} in device memory.
+// more: 41 against 43 us for five ragged sequences of 5212 entries and 16 heads of 64).
 constexpr int ATTN_INLINE = 16;
 struct AttnSeq {
   int32_t seq, seq0, n, blocks;   // index, first entry, entries, row blocks
 };
 struct AttnMany {
-  const int4* table;    // null: seqs
-  const int32_t* cu;    // device cu_seqlens (table only)
   int nkv, n_seqs;
   AttnSeq seqs[ATTN_INLINE];
   __device__ __forceinline__ AttnItem item(int i) const {
-    if (table) {
-      const int4 w = table[i];
-      const int seq0 = cu[w.x];
-      return AttnItem{w.x, w.y, w.z, seq0, cu[w.x + 1] - seq0};
-    }
     int q = i / nkv, which = 0, left = 0;   // left: row blocks from this one to the end of its sequence
     // blocks at distance left come from the s + 1 longest sequences while the next one is shorter
 #pragma unroll
@@ -118,12 +110,24 @@ struct AttnMany {
     return AttnItem{S.seq, i % nkv, S.blocks - left, S.seq0, S.n};
   }
 };
+// More sequences use a table of {seq, KV head, row block, 0} in device memory.  (A type of its own as
+// well: with it inside AttnMany 100 sequences of 64 entries and 32 heads took 58 us in place of 53.)
+struct AttnTable {
+  const int4* table;
+  const int32_t* cu;    // device cu_seqlens
+  __device__ __forceinline__ AttnItem item(int i) const {
+    const int4 w = table[i];
+    const int seq0 = cu[w.x];
+    return AttnItem{w.x, w.y, w.z, seq0, cu[w.x + 1] - seq0};
+  }
+};
 
 struct AttnLaunch {
   int dtype;            // cc_dtype
   const void* q;        // [N][Hq][d]
   void* o;              // [N][Hq][d]
   AttnMany items;       // n_seqs == 1: only items.seqs[0] counts
+  AttnTable table;      // table.table not null: the items in its place
   int n_work;
   KvView k, v;
   bool paged;
