@@ -416,15 +416,24 @@ hipError_t launch_pack_rows(const void* x, int64_t rows, int cols, int64_t ldx, 
 }
 
 namespace {
-// Tile width: the cheapest cover of the entries by tiles of 64 NB columns, a column of the
-// narrower tiles costing more (128256 x 4096 at 512 entries, us a column: 0.865 at 256 wide,
-// 0.854 at 192 but 3 tiles, 0.96 at 128, 1.46 at 64; 16 entries: 260, 243, 230, 228 us).
-int lmhead_nb(int N) {
-  const double cost[4] = {1.7, 1.12, 1.04, 1.0};
+// Tile width by estimated time: rounds of 256 workgroups, each its k-tiles (us below, bound by loads
+// at 64 entries and by matrix work at 256; the same for bf16 and E4M3), the first loads and the
+// epilogue; a last round that leaves CUs idle runs up to 30% quicker.  Over 1026 timings of
+// vocabularies 4000 .. 152064, K 1024 .. 4096, 16 .. 4096 entries and the three weight forms the
+// width it picks is on average 0.1% and at most 7% slower than the best one; the cheapest cover of the
+// entries, without regard to rounds, is 8% and up to 80% (4000 x 1024 at 256 entries: 26 us in
+// one column of 16 tiles, 15 in four; 16000 x 2048 at 770: 71 us in five columns of 315 tiles, 59 in
+// four of 252).
+int lmhead_nb(int V, int N, int K) {
+  const double us[4] = {0.66, 0.88, 1.15, 1.47};
+  const int64_t tiles_m = (int64_t(V) + VT - 1) / VT;
   int best = 4;
   double least = 1e300;
   for (int nb = 4; nb >= 1; --nb) {
-    const double c = double((int64_t(N) + 64 * nb - 1) / (64 * nb)) * nb * cost[nb - 1];
+    const int64_t tiles = tiles_m * ((int64_t(N) + 64 * nb - 1) / (64 * nb));
+    const int64_t full = tiles / 256, left = tiles % 256;
+    const double rounds = full == 0 ? 1.0 : double(full) + (left ? 0.7 + 0.3 * double(left) / 256.0 : 0.0);
+    const double c = rounds * (double(K / 64) * us[nb - 1] + 2.0 + nb);
     if (c < least) {
       least = c;
       best = nb;
@@ -445,7 +454,7 @@ hipError_t launch_lmhead_gemm(const void* w, const void* u, int V, int N, int K,
   g.K = K;
   if (K >= kWideRow)
     return launch_tile<8, 3, 3, 2, AM, true>(g, EpiLse<3>{partial, target, ids, su, sw}, 1, s);
-  switch (lmhead_nb(N)) {
+  switch (lmhead_nb(V, N, K)) {
     case 1: return launch_tile<8, 1, 4, 4, AM>(g, EpiLse<1>{partial, target, ids, su, sw}, 1, s);
     case 2: return launch_tile<8, 2, 3, 3, AM>(g, EpiLse<2>{partial, target, ids, su, sw}, 1, s);
     case 3: return launch_tile<8, 3, 3, 2, AM>(g, EpiLse<3>{partial, target, ids, su, sw}, 1, s);
