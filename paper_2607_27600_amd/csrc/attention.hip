@@ -372,6 +372,9 @@ __global__ __launch_bounds__(256 * KS, 2) void attn_cc_bf16(AttnArgs<Items> a) {
   sa[1] = f32x16{};
 #pragma unroll
   for (int j = 0; j < NS; ++j) sa[j & 1] = mfma32(kfrag(kl0, j), qf[j >> 1], sa[j & 1]);
+  // Every wave has read K(tb) before the first step's DMAs refill its buffer (if any group's do), as
+  // the barrier at the end of a step has it for the tiles after.
+  if (tb0 + 2 * KS < te) __syncthreads();
   float mx = row_max(sa);
 
   // Tile t with parity P = (t - tb) & 1.  S(t) is in sc with its unmasked row max in mx;
