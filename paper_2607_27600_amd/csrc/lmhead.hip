@@ -267,7 +267,7 @@ __global__ __launch_bounds__(256) void quantize_matrix_kernel(const T* __restric
 // entries: a batch of eight is summed against one maximum (a fold tile by tile is a chain of as many
 // exponentials), and few entries take E = 4, for four times the workgroups; beyond, E = 16 reads
 // whole cache lines.  Fold tile by tile in E = 16 -> now: 512 entries of 594 tiles 9.4 -> 6.2 us,
-// 200 entries of 501 tiles 8.6 -> 4.6, 4096 entries (E = 16) 10.0 -> 6.9.
+// 200 entries of 501 tiles 8.6 -> 4.6, 4096 entries (E = 16) 10.0 -> 7.4.
 // The groups fold in one order for either E (pairs, pairs of pairs, up to 16 groups, then the four
 // sums), so that the scores of an entry are the same bits whatever the number of entries beside it.
 constexpr int CMB_G = 64;

@@ -68,7 +68,8 @@ def main(fetch_dir: str, write_dir: str, out: str, cfg_name: str = "C5") -> None
     f_copy = max(_find(f_rows, is_copy))
     w_copy = max(_find(w_rows, is_copy))
     f_lm = _find(f_rows, is_lm)[-1]
-    kernel = [n for n, _ in f_rows if is_lm(n)][-1].split("(")[0].removeprefix("void ")
+    kernel = [n for n, _ in f_rows if is_lm(n)][-1].replace("(anonymous namespace)::", "").split("(")[0]
+    kernel = kernel.removeprefix("void ").replace("cc::", "")
     w_lm = _find(w_rows, is_lm)[-1]
     kf, kw = GIB_KIB / f_copy, GIB_KIB / w_copy
     here = os.path.dirname(os.path.abspath(__file__))
