@@ -256,6 +256,10 @@ __global__ __launch_bounds__(NT, 1) void select_keep_kernel(const float* __restr
   typedef KeepLds<NT, CH> Lds;
   constexpr int NW = Lds::NW, NQ = Lds::NQ, NB = Lds::NB, NC = Lds::NC, DIGIT = Lds::DIGIT;
   constexpr int CHUNK = NT * RCW, TILE = CH * CHUNK, SPT = CH * RCW;
+  // The list holds any bin: the range is taken as it is.  (Without the code for more, these kernels
+  // stay below the 80 scalar registers at which a CU holds one workgroup of 1024 threads in place of
+  // two: 2048 segments of 4096 scores 33 us with it, 21 without.)
+  constexpr bool FITS = !STREAM && TILE <= NC;
   static_assert(SPT <= 32, "one bit per score in a 32-bit mask");
   __shared__ Lds L;
   // With more segments than workgroups each walks several: the stores of one segment drain
@@ -432,7 +436,7 @@ __global__ __launch_bounds__(NT, 1) void select_keep_kernel(const float* __restr
         return __uint_as_float(uint32_t(__builtin_amdgcn_readlane(int(__float_as_uint(whi)), w))) -
                __uint_as_float(uint32_t(__builtin_amdgcn_readlane(int(__float_as_uint(wlo)), w)));
       };
-      if ((STREAM || NC < TILE) && mx - mn > 8.f * fminf(width(0), width(1))) {
+      if (!FITS && mx - mn > 8.f * fminf(width(0), width(1))) {
         const bool has = wlo <= whi;
         const float chi = __uint_as_float(row0_reduce(has ? __float_as_uint(whi) : INF_B, INF_B, fmin_bits));
         const float clo = __uint_as_float(row0_reduce(has ? __float_as_uint(wlo) : NINF_B, NINF_B, fmax_bits));
@@ -492,7 +496,7 @@ __global__ __launch_bounds__(NT, 1) void select_keep_kernel(const float* __restr
         bin = ONE_B + L.sh_key;
         rem = L.sh_rem;   // T is the rem-th largest of the bin's cnt scores
         cnt = L.sh_cnt;
-        if (cnt <= uint32_t(NC) || mn == mx || level == 2) break;
+        if (FITS || cnt <= uint32_t(NC) || mn == mx || level == 2) break;
         // too many for the list (the range has a gap, or is that of a few scores): the bins anew, over
         // the finite scores of this one
         const float was = mx - mn;
@@ -551,7 +555,7 @@ __global__ __launch_bounds__(NT, 1) void select_keep_kernel(const float* __restr
         }
         T = kmin + prefix;
       };
-      if (cnt <= uint32_t(NC)) {
+      if (FITS || cnt <= uint32_t(NC)) {
         tiles([&](uint32_t t0) {
           uint32_t t4 = t0 + RCW * tid;
           asm volatile("" : "+v"(t4));
@@ -579,21 +583,14 @@ __global__ __launch_bounds__(NT, 1) void select_keep_kernel(const float* __restr
         __syncthreads();
         if (cnt <= RANK) {
           // one candidate a wave at a time: its rank is the count of lanes whose candidates compare so
-          uint32_t x[RANK / 64];
-          uint64_t has[RANK / 64];
-#pragma unroll
-          for (int q = 0; q < int(RANK / 64); ++q) {
-            x[q] = L.cand[64 * q + lane];
-            has[q] = __ballot(64 * q + lane < int(cnt));
-          }
           for (uint32_t c = wave; c < cnt; c += NW) {
-            const uint32_t mine = uint32_t(__builtin_amdgcn_readfirstlane(int(L.cand[c])));
+            const uint32_t mine = L.cand[c];
             uint32_t above = 0u, same = 0u;
-#pragma unroll
-            for (int q = 0; q < int(RANK / 64); ++q) {
-              if (64u * q >= cnt) break;
-              above += uint32_t(__popcll(__ballot(x[q] > mine) & has[q]));
-              same += uint32_t(__popcll(__ballot(x[q] == mine) & has[q]));
+#pragma unroll 1
+            for (uint32_t i = lane; i < ((cnt + 63u) & ~63u); i += 64) {   // inside cand (RANK)
+              const uint32_t x = L.cand[i];
+              above += uint32_t(__popcll(__ballot(i < cnt && x > mine)));
+              same += uint32_t(__popcll(__ballot(i < cnt && x == mine)));
             }
             if (lane == 0 && above < rem && rem <= above + same) {   // one value; its holders write the same
               L.sh_key = mine;
@@ -611,7 +608,7 @@ __global__ __launch_bounds__(NT, 1) void select_keep_kernel(const float* __restr
             for (uint32_t i = tid; i < nc; i += NT) visit(L.cand[i]);
           });
         }
-      } else if constexpr (NC < TILE || STREAM) {
+      } else if constexpr (!FITS) {
         search([&](auto&& visit) {
           tiles([&](uint32_t t0) {
             each_score(t0, [&](int j) {
