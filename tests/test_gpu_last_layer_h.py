@@ -60,17 +60,22 @@ def test_small_ragged_all_rows_with_gains_and_positions():
     assert np.all(np.isinf(scores.cpu().numpy()[cu[1:] - 1]))
 
 
-def test_split_k_projections_all_rows():
-    """Shapes whose projections are cut along K (their 256 x 256 tiles fill under half the
-    chip): W_q in 4 slices (hidden 1024), W_o in 4, W_down in 5 with a short last slice
-    (ffn 2944 = 46 k-tiles of 64: four slices of 10 and one of 6), against the oracle on
-    every row."""
+@pytest.mark.parametrize("lens,hq,hkv,keep,cut", [((300, 45), 8, 2, (75, 11), False),
+                                                  ((64, 36), 24, 4, (16, 9), True)])
+def test_split_k_projections_all_rows(lens, hq, hkv, keep, cut):
+    """W_q, W_o and W_down of few tiles and many k-tiles, against the oracle on every row: 345
+    entries, where the plan leaves K in one piece (1024 and 2944 = 46 k-tiles of 64), and 100, where it
+    cuts W_o (3072) and W_down (2944: seven slices of 6 k-tiles and one of 4)."""
     from paper_2607_27600_amd import cc
     from paper_2607_27600_amd.workload import Workload
-    cfg = C.shrink(C.C2H, seq_lens=(300, 45), n_heads_q=8, n_heads_kv=2, hidden=1024,
-                   ffn=2944, vocab=1000, cache_layers=1, keep=(75, 11))
+    cfg = C.shrink(C.C2H, seq_lens=lens, n_heads_q=hq, n_heads_kv=hkv, hidden=1024,
+                   ffn=2944, vocab=1000, cache_layers=1, keep=keep)
     print(f"[last_layer_h] split-K lens={cfg.seq_lens} D={cfg.hidden} F={cfg.ffn}", flush=True)
     w = Workload(cfg, keep_host=True)
+    # what the workspace holds beside the slices, up to roundings of each part
+    n, hd = cfg.n_tokens, hq * cfg.head_dim
+    rest = (n * (cfg.head_dim * 4 + cfg.hidden * 6 + hd * 4 + cfg.ffn * 2) + cc.cc_lmhead_workspace(w.problem))
+    assert (cc.cc_score_workspace(w.problem) - rest >= 2 * n * cfg.hidden * 4) == cut
     scores = torch.full((cfg.n_tokens,), float("nan"), device="cuda")
     cc.cc_score(w.problem, w.inputs(), scores)
     torch.cuda.synchronize()

@@ -92,7 +92,7 @@ def test_packed_lmhead_matches_oracle(lens, D, V):
 
 
 def test_packed_score_two_step_and_fused():
-    """cc_score with lmhead_packed: the two-step mode (packed W_lm, U packed inside) and the
+    """cc_score with lmhead_packed: the two-step mode (packed W_lm, entry rows as they are) and the
     W_o-folded mode (packed W_lm W_o over the attention output)."""
     from paper_2607_27600_amd import cc
     from paper_2607_27600_amd.workload import Workload
